@@ -34,11 +34,19 @@ struct ExtendArgs {
   int layer;
   const int32_t* page_table;
   int max_pages;
-  const ExtendConvDesc* convs;
-  const ExtendTile* tiles;
+  const void* meta;  // device copy of the plan, or nullptr: in the kernel's arguments
+  uint32_t tiles_off;
   const uint16_t* q;
   uint16_t* out;
   float scale_log2;
+  __device__ __forceinline__ ExtendTile tile(int i) const {
+    const auto* p = meta_at<ExtendTile>(meta, tiles_off) + i;
+    return {p->conv, p->q0};
+  }
+  __device__ __forceinline__ ExtendConvDesc conv(int i) const {
+    const auto* p = meta_at<ExtendConvDesc>(meta, 0) + i;
+    return {p->slot, p->len, p->q_len, p->q_row};
+  }
 };
 
 constexpr int kBN = 64;  // keys per tile
@@ -113,8 +121,8 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int tile_idx = block / a.n_kv_heads, g = block % a.n_kv_heads;
-  const ExtendTile tile = a.tiles[tile_idx];
-  const ExtendConvDesc cd = a.convs[tile.conv];
+  const ExtendTile tile = a.tile(tile_idx);
+  const ExtendConvDesc cd = a.conv(tile.conv);
   const int prefix = cd.len - cd.q_len;
   const int q_hi = min(cd.q_len, tile.q0 + BM);
   const int pos_min = prefix + tile.q0, pos_max = prefix + q_hi - 1;
@@ -129,8 +137,7 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
                             static_cast<size_t>(g) * head_stride;
   const size_t page_stride = static_cast<size_t>(a.n_kv_heads) * head_stride;
   const float c = a.scale_log2;
-  const __attribute__((address_space(4))) int32_t* ptc =
-      (const __attribute__((address_space(4))) int32_t*)reinterpret_cast<uintptr_t>(pt);
+  const auto* ptc = as_const(pt);
 
   // ---- copy side: block kb (1 KiB) of a tile = K rows 4kb .. 4kb+3 (page kb / 4) and V^T dims
   // 32 (kb % 4) .. +31 of page kb / 4; this wave copies blocks BPW*wave .. BPW*wave + BPW-1, all of
@@ -333,7 +340,7 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
 
 template <int G>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
-void attn_fwd_kernel(ExtendArgs a) {
+void attn_fwd_kernel(LaunchMeta, ExtendArgs a) {
   attn_fwd_block<G>(a, blockIdx.x);
 }
 
@@ -360,7 +367,7 @@ void mixed_layer_kernel(ExtendArgs ea, int n_ext, DecodeArgs da) {
 // ------------------------------------------------------------------------------------------------
 template <int D, int G, int QT, int BM>
 __global__ __launch_bounds__(64 * G * (BM / (32 * QT))) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1)))
-void attn_fwd_staged_kernel(ExtendArgs a) {
+void attn_fwd_staged_kernel(LaunchMeta, ExtendArgs a) {
   constexpr int NW = G * (BM / (32 * QT));  // waves: G query heads x BM/(32 QT) query blocks
   constexpr int NT = 64 * NW;          // threads
   constexpr int KS = D / 16;           // k-steps of QK^T (16 dims each)
@@ -372,8 +379,8 @@ void attn_fwd_staged_kernel(ExtendArgs a) {
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int tile_idx = blockIdx.x / a.n_kv_heads, g = blockIdx.x % a.n_kv_heads;
-  const ExtendTile tile = a.tiles[tile_idx];
-  const ExtendConvDesc cd = a.convs[tile.conv];
+  const ExtendTile tile = a.tile(tile_idx);
+  const ExtendConvDesc cd = a.conv(tile.conv);
   const int prefix = cd.len - cd.q_len;
   const int q_hi = min(cd.q_len, tile.q0 + BM);              // queries [q0, q_hi)
   const int pos_min = prefix + tile.q0, pos_max = prefix + q_hi - 1;
@@ -396,8 +403,7 @@ void attn_fwd_staged_kernel(ExtendArgs a) {
   // A wave's 64 consecutive chunks always lie in one page, so the page id is wave-uniform and is
   // read with a scalar load: the vector-memory counter then only tracks K/V data, and waiting for
   // a page id never drains K/V loads still in flight for an earlier tile.
-  const __attribute__((address_space(4))) int32_t* ptc =
-      (const __attribute__((address_space(4))) int32_t*)reinterpret_cast<uintptr_t>(pt);
+  const auto* ptc = as_const(pt);
   auto load_tile = [&](int j, uint4 (&kreg)[PER], uint4 (&vreg)[PER]) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -607,18 +613,17 @@ void attn_fwd_staged_kernel(ExtendArgs a) {
 // head_dim 128: 32 queries per wave, eight waves (two per SIMD); head_dim 64: 64 queries
 // per wave, G waves.
 template <int D, int G>
-static void launch_fwd(const ExtendArgs& a, int n_tiles, int n_kv_heads, hipStream_t stream) {
+static void launch_fwd(const LaunchMeta& m, const ExtendArgs& a, int n_tiles, int n_kv_heads, hipStream_t stream) {
   if constexpr (D == 128) {
-    attn_fwd_kernel<G><<<n_tiles * n_kv_heads, 512, 0, stream>>>(a);
+    attn_fwd_kernel<G><<<n_tiles * n_kv_heads, 512, 0, stream>>>(m, a);
   } else {
-    attn_fwd_staged_kernel<D, G, 2, kBM><<<n_tiles * n_kv_heads, 64 * G * (kBM / 64), 0, stream>>>(a);
+    attn_fwd_staged_kernel<D, G, 2, kBM><<<n_tiles * n_kv_heads, 64 * G * (kBM / 64), 0, stream>>>(m, a);
   }
 }
 
 int extend_query_tile(int head_dim, int group) { return head_dim == 128 ? 256 / group : kBM; }
 
-static ExtendArgs make_extend_args(const PoolGeom& g, int layer, const ExtendConvDesc* d_convs,
-                                   const ExtendTile* d_tiles, const void* q, void* out) {
+static ExtendArgs make_extend_args(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q, void* out) {
   ExtendArgs a;
   a.pool = static_cast<const uint16_t*>(g.pool);
   a.n_pages = g.n_pages;
@@ -626,23 +631,25 @@ static ExtendArgs make_extend_args(const PoolGeom& g, int layer, const ExtendCon
   a.layer = layer;
   a.page_table = g.page_table;
   a.max_pages = g.max_pages;
-  a.convs = d_convs;
-  a.tiles = d_tiles;
+  a.meta = e.meta.dev;
+  a.tiles_off = static_cast<uint32_t>(e.tiles_off);
   a.q = static_cast<const uint16_t*>(q);
   a.out = static_cast<uint16_t*>(out);
   a.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(g.head_dim)));
   return a;
 }
 
-hipError_t launch_extend(const PoolGeom& g, int layer, const ExtendConvDesc* d_convs,
-                         const ExtendTile* d_tiles, int n_tiles, const void* q, void* out,
+hipError_t launch_extend(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q, void* out,
                          hipStream_t stream) {
-  if (n_tiles == 0) return hipSuccess;
-  const ExtendArgs a = make_extend_args(g, layer, d_convs, d_tiles, q, out);
+  if (e.n_tiles == 0) return hipSuccess;
+  if (!e.meta.ok()) return hipErrorInvalidValue;
+  const ExtendArgs a = make_extend_args(g, layer, e, q, out);
+  LaunchMeta m;
+  fill_meta(e.meta, &m);
   const int G = g.n_q_heads / g.n_kv_heads;
 #define CS_FWD_CASE(DD, GG)                                   \
   if (g.head_dim == DD && G == GG) {                          \
-    launch_fwd<DD, GG>(a, n_tiles, g.n_kv_heads, stream);     \
+    launch_fwd<DD, GG>(m, a, e.n_tiles, g.n_kv_heads, stream); \
     return hipGetLastError();                                 \
   }
   CS_FWD_CASE(128, 1) CS_FWD_CASE(128, 2) CS_FWD_CASE(128, 4) CS_FWD_CASE(128, 8)
@@ -651,20 +658,17 @@ hipError_t launch_extend(const PoolGeom& g, int layer, const ExtendConvDesc* d_c
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendConvDesc* d_ext_convs,
-                              const ExtendTile* d_tiles, int n_tiles, const void* q_ext,
-                              void* out_ext, const DecodeConvDesc* d_dec_convs,
-                              const int32_t* d_dec_order, int n_dec_convs, int n_items, int split_tokens,
-                              const void* q_dec, float* partials, void* direct_out, hipStream_t stream) {
-  if (g.head_dim != 128 || n_tiles == 0 || n_dec_convs == 0) return hipErrorInvalidValue;
-  if (d_dec_order == nullptr || n_items < n_dec_convs) return hipErrorInvalidValue;
-  if (direct_out != nullptr && n_items != n_dec_convs) return hipErrorInvalidValue;
-  const ExtendArgs ea = make_extend_args(g, layer, d_ext_convs, d_tiles, q_ext, out_ext);
-  DecodeArgs da = make_decode_args(g, layer, d_dec_convs, d_dec_order, n_dec_convs, n_items, split_tokens,
-                                   q_dec, direct_out, partials);
+hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q_ext,
+                              void* out_ext, const DecodeLaunch& w, const void* q_dec, float* partials,
+                              void* direct_out, hipStream_t stream) {
+  if (g.head_dim != 128 || e.n_tiles == 0 || w.n_convs == 0) return hipErrorInvalidValue;
+  if (e.meta.dev == nullptr || w.meta.dev == nullptr || w.n_items < w.n_convs) return hipErrorInvalidValue;
+  if (direct_out != nullptr && w.n_items != w.n_convs) return hipErrorInvalidValue;
+  const ExtendArgs ea = make_extend_args(g, layer, e, q_ext, out_ext);
+  DecodeArgs da = make_decode_args(g, layer, w, q_dec, direct_out, partials);
   da.direct = direct_out != nullptr;
-  const int n_ext = n_tiles * g.n_kv_heads;
-  const int blocks = n_ext + n_items * g.n_kv_heads;
+  const int n_ext = e.n_tiles * g.n_kv_heads;
+  const int blocks = n_ext + w.n_items * g.n_kv_heads;
   switch (g.n_q_heads / g.n_kv_heads) {
     case 1: mixed_layer_kernel<1><<<blocks, 512, 0, stream>>>(ea, n_ext, da); break;
     case 2: mixed_layer_kernel<2><<<blocks, 512, 0, stream>>>(ea, n_ext, da); break;

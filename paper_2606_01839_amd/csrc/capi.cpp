@@ -321,21 +321,36 @@ cs_status upload(cs_pool* p, const void* src, size_t n, void** dev_out) {
   return CS_OK;
 }
 
-// Two host arrays uploaded back to back in one reservation.
-template <typename A, typename B>
-cs_status upload2(cs_pool* p, const std::vector<A>& a, const std::vector<B>& b, A** da, B** db) {
-  const size_t na = align_up(a.size() * sizeof(A), 16), nb = b.size() * sizeof(B);
-  size_t off = 0;
-  cs_status st = ring_reserve(p, na + nb, &off);
-  if (st != CS_OK) return st;
-  if (!a.empty()) std::memcpy(p->h_ring + off, a.data(), a.size() * sizeof(A));
-  if (!b.empty()) std::memcpy(p->h_ring + off + na, b.data(), nb);
-  char* d = p->ws + p->lay.ring + off;
-  CS_HIP(hipMemcpyAsync(d, p->h_ring + off, na + nb, hipMemcpyHostToDevice, p->stream),
-         "hipMemcpyAsync");
-  *da = reinterpret_cast<A*>(d);
-  *db = reinterpret_cast<B*>(d + na);
-  return CS_OK;
+// Launch metadata being laid out on the host: arrays at 16-byte offsets of one block.
+struct Blob {
+  std::vector<char> bytes;
+  template <typename T>
+  size_t push(const T* a, size_t n) {
+    const size_t off = align_up(bytes.size(), 16);
+    bytes.resize(align_up(off + n * sizeof(T), 16));
+    if (n > 0) std::memcpy(bytes.data() + off, a, n * sizeof(T));
+    return off;
+  }
+};
+
+// The block as a launch reads it: in the launch's own arguments if it fits there, else uploaded.
+cs_status place_meta(cs_pool* p, const Blob& b, cs::Meta* m) {
+  m->host = b.bytes.data();
+  m->bytes = b.bytes.size();
+  m->dev = nullptr;
+  if (b.bytes.size() <= cs::kMetaBytes) return CS_OK;
+  void* d = nullptr;
+  cs_status st = upload(p, b.bytes.data(), b.bytes.size(), &d);
+  m->dev = d;
+  return st;
+}
+
+// Part of an uploaded block.
+cs::Meta meta_part(const void* dev, size_t off, size_t bytes) {
+  cs::Meta m;
+  m.dev = static_cast<const char*>(dev) + off;
+  m.bytes = bytes;
+  return m;
 }
 
 cs_status check_convs(const cs_pool* p, int32_t n, const cs_conv* convs, std::vector<const cs::Conv*>& out) {
@@ -360,31 +375,42 @@ size_t wire_size(const cs_pool_desc& d, int64_t len) {
 
 hipStream_t as_stream(cs_stream s) { return reinterpret_cast<hipStream_t>(s); }
 
-// Extend/prefill work uploaded once and launchable for any layer.
+// Extend/prefill work, launchable for any layer: one part, or several where the tiles exceed one
+// quarter of the ring. `blobs` keeps the bytes of parts that travel in the launch arguments.
 struct ExtendWork {
-  struct Part {
-    cs::ExtendConvDesc* convs;
-    cs::ExtendTile* tiles;
-    int n_tiles;
-  };
-  std::vector<Part> parts;
+  std::vector<cs::ExtendLaunch> parts;
+  std::vector<Blob> blobs;
 };
 
-cs_status upload_extend(cs_pool* p, const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
-                        const std::vector<int32_t>& q_lens, ExtendWork* w) {
+cs::ExtendPlan plan_extend_batch(const cs_pool* p, const std::vector<int32_t>& slots,
+                                 const std::vector<int64_t>& lens, const std::vector<int32_t>& q_lens) {
   const int tile = cs::extend_query_tile(p->desc.head_dim, p->desc.n_q_heads / p->desc.n_kv_heads);
-  cs::ExtendPlan plan = cs::plan_extend(slots, lens, q_lens, tile);
+  return cs::plan_extend(slots, lens, q_lens, tile);
+}
+
+// Tiles [t0, t1) of a plan with its conversations, laid out at the end of the block; offsets of
+// the launch are relative to *off.
+cs::ExtendLaunch push_extend(const cs::ExtendPlan& plan, size_t t0, size_t t1, Blob* b, size_t* off) {
+  cs::ExtendLaunch e;
+  *off = b->push(plan.convs.data(), plan.convs.size());
+  e.tiles_off = b->push(plan.tiles.data() + t0, t1 - t0) - *off;
+  e.n_tiles = static_cast<int>(t1 - t0);
+  return e;
+}
+
+cs_status upload_extend(cs_pool* p, const cs::ExtendPlan& plan, ExtendWork* w) {
   const size_t desc_bytes = align_up(plan.convs.size() * sizeof(cs::ExtendConvDesc), 16);
   if (desc_bytes + kAlign + sizeof(cs::ExtendTile) > kQuarter)
     return fail(CS_ENOMEM, "batch descriptor exceeds the metadata ring");
   const size_t max_tiles = (kQuarter - desc_bytes - kAlign) / sizeof(cs::ExtendTile);
   for (size_t t0 = 0; t0 < plan.tiles.size(); t0 += max_tiles) {
-    const size_t t1 = std::min(plan.tiles.size(), t0 + max_tiles);
-    std::vector<cs::ExtendTile> part(plan.tiles.begin() + t0, plan.tiles.begin() + t1);
-    ExtendWork::Part pw{nullptr, nullptr, static_cast<int>(part.size())};
-    cs_status st = upload2(p, plan.convs, part, &pw.convs, &pw.tiles);
+    Blob b;
+    size_t off = 0;
+    cs::ExtendLaunch e = push_extend(plan, t0, std::min(plan.tiles.size(), t0 + max_tiles), &b, &off);
+    cs_status st = place_meta(p, b, &e.meta);
     if (st != CS_OK) return st;
-    w->parts.push_back(pw);
+    w->parts.push_back(e);
+    w->blobs.push_back(std::move(b));   // moving a vector keeps its buffer, which e.meta.host points to
   }
   return CS_OK;
 }
@@ -392,19 +418,17 @@ cs_status upload_extend(cs_pool* p, const std::vector<int32_t>& slots, const std
 cs_status launch_extend_layer(cs_pool* p, const ExtendWork& w, int layer, const void* q, void* out,
                               hipStream_t s) {
   const cs::PoolGeom g = p->geom();
-  for (const auto& pw : w.parts) {
-    cs_status st = timed_launch_on(p, s, CS_PROF_ATTN_FWD, "attention launch", [&] {
-      return cs::launch_extend(g, layer, pw.convs, pw.tiles, pw.n_tiles, q, out, s);
-    });
+  for (const auto& e : w.parts) {
+    cs_status st = timed_launch_on(p, s, CS_PROF_ATTN_FWD, "attention launch",
+                                   [&] { return cs::launch_extend(g, layer, e, q, out, s); });
     if (st != CS_OK) return st;
   }
   return CS_OK;
 }
 
 struct DecodeWork {
-  cs::DecodeConvDesc* convs = nullptr;
-  int32_t* order = nullptr;  // launch order of the items
-  int n_convs = 0, n_items = 0, split = 0;
+  cs::DecodeLaunch w;
+  Blob blob;
   bool single = false;  // one work item per conversation: the split writes the output directly
 };
 
@@ -413,7 +437,7 @@ cs::DecodePlan plan_decode_batch(const cs_pool* p, const std::vector<int32_t>& s
   return cs::plan_decode(slots, lens, p->desc.n_kv_heads, kDecodeTargetItems);
 }
 
-// Descriptors and launch order of a decode plan, as uploaded back to back.
+// Descriptors and launch order of a decode plan, as laid out back to back.
 size_t decode_upload_bytes(const cs::DecodePlan& plan) {
   return align_up(plan.convs.size() * sizeof(cs::DecodeConvDesc), 16) + plan.order.size() * sizeof(int32_t);
 }
@@ -424,27 +448,33 @@ cs_status check_decode_plan(const cs_pool* p, const cs::DecodePlan& plan) {
   return CS_OK;
 }
 
-cs_status upload_decode(cs_pool* p, const cs::DecodePlan& plan, DecodeWork* w) {
-  cs_status st = check_decode_plan(p, plan);
-  if (st != CS_OK) return st;
-  if ((st = upload2(p, plan.convs, plan.order, &w->convs, &w->order)) != CS_OK) return st;
-  w->n_convs = static_cast<int>(plan.convs.size());
-  w->n_items = plan.n_items;
-  w->split = plan.split_tokens;
-  w->single = plan.single_item;
-  return CS_OK;
+// A plan laid out at the end of the block; offsets of the launch are relative to *off.
+cs::DecodeLaunch push_decode(const cs::DecodePlan& plan, Blob* b, size_t* off) {
+  cs::DecodeLaunch w;
+  *off = b->push(plan.convs.data(), plan.convs.size());
+  w.order_off = b->push(plan.order.data(), plan.order.size()) - *off;
+  w.n_convs = static_cast<int>(plan.convs.size());
+  w.n_items = plan.n_items;
+  w.split = plan.split_tokens;
+  return w;
+}
+
+cs_status place_decode(cs_pool* p, const cs::DecodePlan& plan, DecodeWork* dw) {
+  size_t off = 0;
+  dw->w = push_decode(plan, &dw->blob, &off);
+  dw->single = plan.single_item;
+  return place_meta(p, dw->blob, &dw->w.meta);
 }
 
 // Split, then merge; when every conversation is one work item the split writes the output itself.
 cs_status launch_decode_layer(cs_pool* p, const DecodeWork& w, int layer, const void* q, void* out) {
   const cs::PoolGeom g = p->geom();
   cs_status st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
-    return cs::launch_decode_split(g, layer, w.convs, w.order, w.n_convs, w.n_items, w.split, q, p->partials(),
-                                   w.single ? out : nullptr, p->stream);
+    return cs::launch_decode_split(g, layer, w.w, q, p->partials(), w.single ? out : nullptr, p->stream);
   });
   if (st != CS_OK || w.single) return st;
   return timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch", [&] {
-    return cs::launch_decode_merge(g, w.convs, w.n_convs, p->partials(), out, p->stream);
+    return cs::launch_decode_merge(g, w.w, p->partials(), out, p->stream);
   });
 }
 
@@ -479,19 +509,15 @@ cs_status attend(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t* q_l
     lens[i] = cv[i]->len;
   }
   ExtendWork w;
-  if ((st = upload_extend(p, slots, lens, ql, &w)) != CS_OK) return st;
+  if ((st = upload_extend(p, plan_extend_batch(p, slots, lens, ql), &w)) != CS_OK) return st;
   return launch_extend_layer(p, w, layer, q, out, p->stream);
 }
 
-cs_status append_impl(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t* n_new,
-                      const void* k, const void* v, cs_stream stream) {
-  if (!p) return fail(CS_EINVAL, "null pool");
-  std::vector<const cs::Conv*> cv;
-  cs_status st = check_convs(p, n, convs, cv);
-  if (st != CS_OK) return st;
-  if (n > 0 && !n_new) return fail(CS_EINVAL, "null n_new");
+// Whether the conversations can take n_new[i] tokens each (nothing is changed); *total = their sum.
+cs_status check_append(const cs_pool* p, const std::vector<const cs::Conv*>& cv, const int32_t* n_new, const void* k,
+                       const void* v, int64_t* total_out) {
   int64_t total = 0, need_pages = 0;
-  for (int32_t i = 0; i < n; ++i) {
+  for (size_t i = 0; i < cv.size(); ++i) {
     if (n_new[i] < 0) return fail(CS_EINVAL, "negative token count");
     const int64_t nl = cv[i]->len + n_new[i];
     if (cs::pages_for(nl) > p->desc.max_pages_per_conv)
@@ -499,12 +525,28 @@ cs_status append_impl(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t
     need_pages += cs::pages_for(nl) - cs::pages_for(cv[i]->len);
     total += n_new[i];
   }
+  *total_out = total;
   if (total == 0) return CS_OK;
   if (total > INT32_MAX) return fail(CS_EINVAL, "too many tokens in one append");
   if (!k || !v) return fail(CS_EINVAL, "null k/v");
   if (need_pages > p->pages.free_count())
     return fail(CS_ENOMEM, "KV pool exhausted: need " + std::to_string(need_pages) + " pages, " +
                                std::to_string(p->pages.free_count()) + " free");
+  return CS_OK;
+}
+
+// `carry` (may be null): metadata of the launches that follow the append in the same call; on success
+// *carry_dev is its device address.
+cs_status append_impl(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t* n_new,
+                      const void* k, const void* v, cs_stream stream, const Blob* carry = nullptr,
+                      void** carry_dev = nullptr) {
+  if (!p) return fail(CS_EINVAL, "null pool");
+  std::vector<const cs::Conv*> cv;
+  cs_status st = check_convs(p, n, convs, cv);
+  if (st != CS_OK) return st;
+  if (n > 0 && !n_new) return fail(CS_EINVAL, "null n_new");
+  int64_t total = 0;
+  if ((st = check_append(p, cv, n_new, k, v, &total)) != CS_OK || total == 0) return st;
   if ((st = ensure_device(p)) != CS_OK) return st;
   if ((st = use_stream(p, as_stream(stream))) != CS_OK) return st;
 
@@ -538,20 +580,43 @@ cs_status append_impl(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t
   };
 
   const cs::PoolGeom g = p->geom();
-  const size_t per = kQuarter / sizeof(cs::PageChunk) - 1;
-  for (size_t c0 = 0; c0 < chunks.size(); c0 += per) {
-    const size_t c1 = std::min(chunks.size(), c0 + per);
-    void* d = nullptr;
-    st = upload(p, chunks.data() + c0, (c1 - c0) * sizeof(cs::PageChunk), &d);
-    if (st == CS_OK)
-      st = timed_launch(p, CS_PROF_APPEND, "append launch", [&] {
-        return cs::launch_append(g, static_cast<const cs::PageChunk*>(d), static_cast<int>(c1 - c0), k, v,
-                                 total, p->stream);
-      });
-    if (st != CS_OK) {
-      roll_back();
-      return st;
+  const size_t carry_bytes = carry ? carry->bytes.size() : 0;
+  auto launch = [&](const cs::Meta& m, int n_chunks, const cs::AppendCarry& c) {
+    return timed_launch(p, CS_PROF_APPEND, "append launch",
+                        [&] { return cs::launch_append(g, m, n_chunks, c, k, v, total, p->stream); });
+  };
+  if (chunks.size() * sizeof(cs::PageChunk) + carry_bytes <= cs::kMetaBytes) {
+    // small: the chunks travel in the launch's arguments, and so does the metadata of the launches
+    // that follow, which the append kernel stores to the ring's device half.
+    Blob b;
+    b.push(chunks.data(), chunks.size());
+    cs::AppendCarry c;
+    if (carry_bytes > 0) {
+      size_t off = 0;
+      st = ring_reserve(p, carry_bytes, &off);
+      c.dst = p->ws + p->lay.ring + off;
+      c.bytes = carry_bytes;
+      c.off = b.push(carry->bytes.data(), carry_bytes);
+      *carry_dev = c.dst;
     }
+    cs::Meta m;
+    m.host = b.bytes.data();
+    m.bytes = b.bytes.size();
+    if (st == CS_OK) st = launch(m, static_cast<int>(chunks.size()), c);
+  } else {
+    if (carry_bytes > 0) st = upload(p, carry->bytes.data(), carry_bytes, carry_dev);
+    const size_t per = kQuarter / sizeof(cs::PageChunk) - 1;
+    for (size_t c0 = 0; c0 < chunks.size() && st == CS_OK; c0 += per) {
+      const size_t c1 = std::min(chunks.size(), c0 + per);
+      void* d = nullptr;
+      st = upload(p, chunks.data() + c0, (c1 - c0) * sizeof(cs::PageChunk), &d);
+      if (st == CS_OK)
+        st = launch(meta_part(d, 0, (c1 - c0) * sizeof(cs::PageChunk)), static_cast<int>(c1 - c0), {});
+    }
+  }
+  if (st != CS_OK) {
+    roll_back();
+    return st;
   }
   for (int32_t i = 0; i < n; ++i) p->convs.find(convs[i])->len += n_new[i];
   return CS_OK;
@@ -695,8 +760,10 @@ cs_status cs_attn_decode_batch(cs_pool* p, int32_t n, const cs_conv* convs, int3
     slots[i] = cs::ConvTable::slot_of(convs[i]);
     lens[i] = cv[i]->len;
   }
+  const cs::DecodePlan plan = plan_decode_batch(p, slots, lens);
+  if ((st = check_decode_plan(p, plan)) != CS_OK) return st;
   DecodeWork w;
-  if ((st = upload_decode(p, plan_decode_batch(p, slots, lens), &w)) != CS_OK) return st;
+  if ((st = place_decode(p, plan, &w)) != CS_OK) return st;
   return launch_decode_layer(p, w, layer, q, out);
 }
 
@@ -734,15 +801,13 @@ cs_status cs_attn_decode_batch_noalloc(cs_pool* p, int32_t n, const cs_conv* con
   CS_HIP(cs::static_decode_scratch(&scratch), "hipGetSymbolAddress(decode scratch)");
   if ((st = use_stream(p, as_stream(stream))) != CS_OK) return st;
   DecodeWork w;
-  if ((st = upload2(p, plan.convs, plan.order, &w.convs, &w.order)) != CS_OK) return st;
+  if ((st = place_decode(p, plan, &w)) != CS_OK) return st;
   const cs::PoolGeom g = p->geom();
   // untimed launches: the timing events of cs_profile_* would be created on demand
-  CS_HIP(cs::launch_decode_split(g, layer, w.convs, w.order, static_cast<int>(plan.convs.size()), plan.n_items,
-                                 plan.split_tokens, q, scratch, plan.single_item ? out : nullptr, p->stream),
+  CS_HIP(cs::launch_decode_split(g, layer, w.w, q, scratch, w.single ? out : nullptr, p->stream),
          "decode split launch");
-  if (plan.single_item) return CS_OK;
-  CS_HIP(cs::launch_decode_merge(g, w.convs, static_cast<int>(plan.convs.size()), scratch, out, p->stream),
-         "decode merge launch");
+  if (w.single) return CS_OK;
+  CS_HIP(cs::launch_decode_merge(g, w.w, scratch, out, p->stream), "decode merge launch");
   return CS_OK;
 }
 
@@ -793,10 +858,12 @@ cs_status cs_kv_unpack(cs_pool* p, const void* src, size_t src_bytes, int64_t n_
   const size_t per = kQuarter / sizeof(int32_t) - 64;
   for (size_t p0 = 0; p0 < c->pages.size(); p0 += per) {
     const size_t p1 = std::min(c->pages.size(), p0 + per);
-    void* d = nullptr;
-    if ((st = upload(p, c->pages.data() + p0, (p1 - p0) * sizeof(int32_t), &d)) != CS_OK) return st;
+    Blob b;
+    b.push(c->pages.data() + p0, p1 - p0);
+    cs::Meta m;
+    if ((st = place_meta(p, b, &m)) != CS_OK) return st;
     st = timed_launch(p, CS_PROF_UNPACK, "unpack launch", [&] {
-      return cs::launch_unpack(p->geom(), src, static_cast<const int32_t*>(d), cs::ConvTable::slot_of(h),
+      return cs::launch_unpack(p->geom(), src, m, cs::ConvTable::slot_of(h),
                                n_tokens, static_cast<int>(p0), static_cast<int>(p1 - p0), p->stream);
     });
     if (st != CS_OK) return st;
@@ -847,19 +914,37 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     d_plan = plan_decode_batch(p, d_slots, d_lens);
     if ((st = check_decode_plan(p, d_plan)) != CS_OK) return st;
   }
-  // append every new token (all layers); validates capacity and commits the host metadata
-  if ((st = append_impl(p, static_cast<int32_t>(all.size()), all.data(), n_new.data(), k, v, stream)) != CS_OK)
-    return st;
+  int64_t total = 0;
+  if ((st = check_append(p, cv, n_new.data(), k, v, &total)) != CS_OK) return st;
+  // The step's plans, laid out in one block that goes to the device with the append.
   std::vector<int32_t> e_slots(n_ext), e_q(n_new.begin(), n_new.begin() + n_ext);
   std::vector<int64_t> e_lens(n_ext);
   for (int32_t i = 0; i < n_ext; ++i) {
     e_slots[i] = cs::ConvTable::slot_of(ext_convs[i]);
-    e_lens[i] = p->convs.find(ext_convs[i])->len;
+    e_lens[i] = cv[i]->len + ext_lens[i];
   }
+  const cs::ExtendPlan e_plan = plan_extend_batch(p, e_slots, e_lens, e_q);
+  Blob blob;
   ExtendWork ew;
   DecodeWork dw;
-  if (n_ext > 0 && (st = upload_extend(p, e_slots, e_lens, e_q, &ew)) != CS_OK) return st;
-  if (n_dec > 0 && (st = upload_decode(p, d_plan, &dw)) != CS_OK) return st;
+  size_t e_off = 0, d_off = 0;
+  if (n_dec > 0) {
+    dw.w = push_decode(d_plan, &blob, &d_off);
+    dw.single = d_plan.single_item;
+  }
+  const size_t d_bytes = blob.bytes.size();
+  // an extend plan that does not fit beside the decode plan is uploaded by itself, maybe in parts
+  const bool e_carried = n_ext > 0 && d_bytes + e_plan.convs.size() * sizeof(cs::ExtendConvDesc) +
+                                              e_plan.tiles.size() * sizeof(cs::ExtendTile) + 64 <= kQuarter;
+  if (e_carried) ew.parts.push_back(push_extend(e_plan, 0, e_plan.tiles.size(), &blob, &e_off));
+  // append every new token (all layers); validates capacity and commits the host metadata
+  void* dev = nullptr;
+  if ((st = append_impl(p, static_cast<int32_t>(all.size()), all.data(), n_new.data(), k, v, stream, &blob, &dev)) !=
+      CS_OK)
+    return st;
+  if (n_dec > 0) dw.w.meta = meta_part(dev, d_off, d_bytes);
+  if (e_carried) ew.parts[0].meta = meta_part(dev, e_off, blob.bytes.size() - e_off);
+  if (n_ext > 0 && !e_carried && (st = upload_extend(p, e_plan, &ew)) != CS_OK) return st;
   const size_t row_bytes = static_cast<size_t>(p->desc.n_q_heads) * p->desc.head_dim * 2;
   const int nl = p->desc.n_layers;
   const size_t ext_layer_bytes = static_cast<size_t>(ext_rows) * row_bytes;
@@ -892,16 +977,14 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     // As in a model forward pass, one layer after the other; each layer is one launch with its
     // extend tiles and its decode split, then the decode merge.
     const cs::PoolGeom g = p->geom();
-    const auto& pw = ew.parts[0];
     for (int layer = 0; layer < nl && st == CS_OK; ++layer) {
       st = timed_launch(p, CS_PROF_MIXED_LAYER, "mixed layer launch", [&] {
-        return cs::launch_mixed_layer(g, layer, pw.convs, pw.tiles, pw.n_tiles, q_e(layer), o_e(layer),
-                                      dw.convs, dw.order, dw.n_convs, dw.n_items, dw.split, q_d(layer),
-                                      p->partials(), dw.single ? o_d(layer) : nullptr, p->stream);
+        return cs::launch_mixed_layer(g, layer, ew.parts[0], q_e(layer), o_e(layer), dw.w, q_d(layer), p->partials(),
+                                      dw.single ? o_d(layer) : nullptr, p->stream);
       });
       if (st == CS_OK && !dw.single)
         st = timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch", [&] {
-          return cs::launch_decode_merge(g, dw.convs, dw.n_convs, p->partials(), o_d(layer), p->stream);
+          return cs::launch_decode_merge(g, dw.w, p->partials(), o_d(layer), p->stream);
         });
     }
     return st;
@@ -935,8 +1018,7 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     st = span_begin(p, p->stream, CS_PROF_DECODE_SPLIT);
     for (int layer = 0; layer < nl && st == CS_OK; ++layer)
       st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
-        return cs::launch_decode_split(g, layer, dw.convs, dw.order, dw.n_convs, dw.n_items, dw.split, q_d(layer),
-                                       p->partials(), o_d(layer), p->stream);
+        return cs::launch_decode_split(g, layer, dw.w, q_d(layer), p->partials(), o_d(layer), p->stream);
       });
     if (const cs_status se = span_end(p); st == CS_OK) st = se;
   } else if (n_dec > 0 && st == CS_OK) {
@@ -944,21 +1026,18 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     float* buf[2] = {p->partials(), p->partials2()};
     st = span_begin(p, p->stream, CS_PROF_DECODE_SPLIT);
     if (st == CS_OK) st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
-      return cs::launch_decode_split(g, 0, dw.convs, dw.order, dw.n_convs, dw.n_items, dw.split, q_d(0), buf[0],
-                                     nullptr, p->stream);
+      return cs::launch_decode_split(g, 0, dw.w, q_d(0), buf[0], nullptr, p->stream);
     });
     for (int layer = 1; layer < nl && st == CS_OK; ++layer) {
       st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode merge+split launch", [&] {
-        return cs::launch_decode_merge_split(g, layer, dw.convs, dw.order, dw.n_convs, dw.n_items, dw.split,
-                                             q_d(layer), buf[layer % 2], buf[(layer - 1) % 2],
+        return cs::launch_decode_merge_split(g, layer, dw.w, q_d(layer), buf[layer % 2], buf[(layer - 1) % 2],
                                              o_d(layer - 1), p->stream);
       });
     }
     if (const cs_status se = span_end(p); st == CS_OK) st = se;
     if (st == CS_OK)
       st = timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch", [&] {
-        return cs::launch_decode_merge(g, dw.convs, dw.n_convs, buf[(nl - 1) % 2], o_d(nl - 1),
-                                       p->stream);
+        return cs::launch_decode_merge(g, dw.w, buf[(nl - 1) % 2], o_d(nl - 1), p->stream);
       });
   }
   if (fork) {  // join even after a failed launch, so later work never overtakes the side stream

@@ -71,7 +71,7 @@ __device__ __forceinline__ void merge_body(const DecodeArgs& a, const int b, con
   constexpr int SG = 256 / DV;       // record groups
   constexpr int R = partial_floats(D);
   const int g = h / a.group, c = h % a.group;
-  const DecodeConvDesc cd = load_desc(as_const(a.convs) + (valid ? b : 0));
+  const DecodeConvDesc cd = load_desc(a.convs() + (valid ? b : 0));
   const int lane = tid & 63, wave = tid >> 6;
   const size_t split_stride = static_cast<size_t>(a.n_kv_heads) * a.group * R;
   const float* base =
@@ -114,13 +114,13 @@ __device__ __forceinline__ void merge_body(const DecodeArgs& a, const int b, con
 }
 
 template <int D>
-__global__ __launch_bounds__(kDecodeItemThreads) void decode_split_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(kDecodeItemThreads) void decode_split_kernel(LaunchMeta, DecodeArgs a) {
   __shared__ float xch[split_exchange_floats<D>()];
   split_body<D>(a, blockIdx.x, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), xch);
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void decode_merge_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(256) void decode_merge_kernel(LaunchMeta, DecodeArgs a) {
   __shared__ MergeLds<D> lds;
   merge_body<D>(a, blockIdx.x, blockIdx.y, threadIdx.x, lds, true);
 }
@@ -146,35 +146,32 @@ __global__ __launch_bounds__(kDecodeItemThreads) void decode_merge_split_kernel(
   }
 }
 
-hipError_t launch_decode_split(const PoolGeom& g, int layer, const DecodeConvDesc* d_convs,
-                               const int32_t* d_order, int n_convs, int n_items, int split_tokens,
-                               const void* q, float* partials, void* direct_out, hipStream_t stream) {
-  if (n_convs == 0) return hipSuccess;
-  if (d_order == nullptr || n_items < n_convs) return hipErrorInvalidValue;
-  DecodeArgs a = make_decode_args(g, layer, d_convs, d_order, n_convs, n_items, split_tokens, q, direct_out,
-                                  partials);
-  a.direct = direct_out != nullptr && n_items == n_convs;
+hipError_t launch_decode_split(const PoolGeom& g, int layer, const DecodeLaunch& w, const void* q, float* partials,
+                               void* direct_out, hipStream_t stream) {
+  if (w.n_convs == 0) return hipSuccess;
+  if (!w.meta.ok() || w.n_items < w.n_convs) return hipErrorInvalidValue;
+  DecodeArgs a = make_decode_args(g, layer, w, q, direct_out, partials);
+  a.direct = direct_out != nullptr && w.n_items == w.n_convs;
   if (direct_out != nullptr && !a.direct) return hipErrorInvalidValue;
-  const int blocks = n_items * g.n_kv_heads;
-  if (g.head_dim == 128) decode_split_kernel<128><<<blocks, kDecodeItemThreads, 0, stream>>>(a);
-  else if (g.head_dim == 64) decode_split_kernel<64><<<blocks, kDecodeItemThreads, 0, stream>>>(a);
+  LaunchMeta m;
+  fill_meta(w.meta, &m);
+  const int blocks = w.n_items * g.n_kv_heads;
+  if (g.head_dim == 128) decode_split_kernel<128><<<blocks, kDecodeItemThreads, 0, stream>>>(m, a);
+  else if (g.head_dim == 64) decode_split_kernel<64><<<blocks, kDecodeItemThreads, 0, stream>>>(m, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_decode_merge_split(const PoolGeom& g, int split_layer, const DecodeConvDesc* d_convs,
-                                     const int32_t* d_order, int n_convs, int n_items, int split_tokens,
-                                     const void* q, float* split_partials, const float* merge_partials,
-                                     void* merge_out, hipStream_t stream) {
-  if (n_convs == 0) return hipSuccess;
-  if (d_order == nullptr || n_items < n_convs) return hipErrorInvalidValue;
-  const DecodeArgs as = make_decode_args(g, split_layer, d_convs, d_order, n_convs, n_items, split_tokens, q,
-                                         nullptr, split_partials);
-  const DecodeArgs am = make_decode_args(g, 0, d_convs, nullptr, n_convs, 0, 0, nullptr, merge_out,
-                                         merge_partials);
+hipError_t launch_decode_merge_split(const PoolGeom& g, int split_layer, const DecodeLaunch& w, const void* q,
+                                     float* split_partials, const float* merge_partials, void* merge_out,
+                                     hipStream_t stream) {
+  if (w.n_convs == 0) return hipSuccess;
+  if (w.meta.dev == nullptr || w.n_items < w.n_convs) return hipErrorInvalidValue;
+  const DecodeArgs as = make_decode_args(g, split_layer, w, q, nullptr, split_partials);
+  const DecodeArgs am = make_decode_args(g, 0, w, nullptr, merge_out, merge_partials);
   constexpr int kPerBlock = kDecodeItemThreads / 256;
-  const int merge_blocks = (n_convs * g.n_q_heads + kPerBlock - 1) / kPerBlock;
-  const int blocks = merge_blocks + n_items * g.n_kv_heads;
+  const int merge_blocks = (w.n_convs * g.n_q_heads + kPerBlock - 1) / kPerBlock;
+  const int blocks = merge_blocks + w.n_items * g.n_kv_heads;
   if (g.head_dim == 128)
     decode_merge_split_kernel<128><<<blocks, kDecodeItemThreads, 0, stream>>>(am, as, merge_blocks);
   else if (g.head_dim == 64)
@@ -183,13 +180,16 @@ hipError_t launch_decode_merge_split(const PoolGeom& g, int split_layer, const D
   return hipGetLastError();
 }
 
-hipError_t launch_decode_merge(const PoolGeom& g, const DecodeConvDesc* d_convs, int n_convs,
-                               const float* partials, void* out, hipStream_t stream) {
-  if (n_convs == 0) return hipSuccess;
-  const DecodeArgs a = make_decode_args(g, 0, d_convs, nullptr, n_convs, 0, 0, nullptr, out, partials);
-  const dim3 grid(n_convs, g.n_q_heads);
-  if (g.head_dim == 128) decode_merge_kernel<128><<<grid, 256, 0, stream>>>(a);
-  else if (g.head_dim == 64) decode_merge_kernel<64><<<grid, 256, 0, stream>>>(a);
+hipError_t launch_decode_merge(const PoolGeom& g, const DecodeLaunch& w, const float* partials, void* out,
+                               hipStream_t stream) {
+  if (w.n_convs == 0) return hipSuccess;
+  if (!w.meta.ok()) return hipErrorInvalidValue;
+  const DecodeArgs a = make_decode_args(g, 0, w, nullptr, out, partials);
+  LaunchMeta m;
+  fill_meta(w.meta, &m);
+  const dim3 grid(w.n_convs, g.n_q_heads);
+  if (g.head_dim == 128) decode_merge_kernel<128><<<grid, 256, 0, stream>>>(m, a);
+  else if (g.head_dim == 64) decode_merge_kernel<64><<<grid, 256, 0, stream>>>(m, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -17,7 +17,8 @@ struct DecodeArgs {
   int layer;
   const int32_t* page_table;
   int max_pages;
-  const DecodeConvDesc* convs;
+  const void* meta;  // device copy of the plan, or nullptr: in the kernel's arguments
+  uint32_t order_off;
   int n_convs;
   int n_items;  // work items of the plan (kDecodeSubSplits splits each)
   int split;    // keys per split (per wave), multiple of 32, <= 1024
@@ -26,17 +27,12 @@ struct DecodeArgs {
   int direct;       // every conversation is one item: write the output instead of a record
   float* partials;  // [n_items * n_kv_heads][group] records of partial_floats(D), one per item
   float scale_log2;
-  const int32_t* order;  // [n_items]: workgroup w takes item order[w / n_kv_heads]
+  __device__ __forceinline__ ConstPtr<DecodeConvDesc> convs() const { return meta_at<DecodeConvDesc>(meta, 0); }
+  // [n_items]: workgroup w takes item order[w / n_kv_heads]
+  __device__ __forceinline__ ConstPtr<int32_t> order() const { return meta_at<int32_t>(meta, order_off); }
 };
 
-// Kernel arguments read by every wave alike are loaded through the constant address space, so
-// they land in scalar registers and the loop control, page bases and addresses stay wave-uniform.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(4))) T* as_const(const T* p) {
-  return (const __attribute__((address_space(4))) T*)reinterpret_cast<uintptr_t>(p);
-}
-
-__device__ __forceinline__ DecodeConvDesc load_desc(const __attribute__((address_space(4))) DecodeConvDesc* p) {
+__device__ __forceinline__ DecodeConvDesc load_desc(ConstPtr<DecodeConvDesc> p) {
   DecodeConvDesc d;
   d.slot = p->slot;
   d.len = p->len;
@@ -45,8 +41,7 @@ __device__ __forceinline__ DecodeConvDesc load_desc(const __attribute__((address
   return d;
 }
 
-__device__ __forceinline__ int find_conv(const __attribute__((address_space(4))) DecodeConvDesc* convs,
-                                         int n, int item) {
+__device__ __forceinline__ int find_conv(ConstPtr<DecodeConvDesc> convs, int n, int item) {
   int lo = 0, hi = n - 1;
   while (lo < hi) {  // largest b with item_start <= item
     int mid = (lo + hi + 1) >> 1;
@@ -80,8 +75,8 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
   constexpr int DT = D / 16;  // 16-dim tiles of the output
   const int lane = threadIdx.x & 63;
   const bool valid = work < a.n_items * a.n_kv_heads;
-  const int item = as_const(a.order)[valid ? work / a.n_kv_heads : 0], g = work % a.n_kv_heads;
-  const auto* convs = as_const(a.convs);
+  const int item = a.order()[valid ? work / a.n_kv_heads : 0], g = work % a.n_kv_heads;
+  const auto* convs = a.convs();
   const int conv_idx = find_conv(convs, a.n_convs, item);
   const DecodeConvDesc cd = load_desc(convs + conv_idx);
   const int item_k0 = (item - cd.item_start) * kDecodeSubSplits * a.split;
@@ -249,9 +244,8 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
   }
 }
 
-inline DecodeArgs make_decode_args(const PoolGeom& g, int layer, const DecodeConvDesc* d_convs,
-                                   const int32_t* d_order, int n_convs, int n_items, int split_tokens,
-                                   const void* q, void* out, const float* partials) {
+inline DecodeArgs make_decode_args(const PoolGeom& g, int layer, const DecodeLaunch& w, const void* q, void* out,
+                                   const float* partials) {
   DecodeArgs a;
   a.pool = static_cast<const uint16_t*>(g.pool);
   a.n_pages = g.n_pages;
@@ -260,11 +254,11 @@ inline DecodeArgs make_decode_args(const PoolGeom& g, int layer, const DecodeCon
   a.layer = layer;
   a.page_table = g.page_table;
   a.max_pages = g.max_pages;
-  a.convs = d_convs;
-  a.order = d_order;
-  a.n_convs = n_convs;
-  a.n_items = n_items;
-  a.split = split_tokens;
+  a.meta = w.meta.dev;
+  a.order_off = static_cast<uint32_t>(w.order_off);
+  a.n_convs = w.n_convs;
+  a.n_items = w.n_items;
+  a.split = w.split;
   a.q = static_cast<const uint16_t*>(q);
   a.out = static_cast<uint16_t*>(out);
   a.partials = const_cast<float*>(partials);

@@ -99,6 +99,23 @@ __device__ __forceinline__ float halves_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Data every wave reads alike is loaded through the constant address space, so it lands in scalar
+// registers and loop control, page bases and addresses stay wave-uniform.
+template <typename T>
+using ConstPtr = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ __forceinline__ ConstPtr<T> as_const(const T* p) {
+  return (ConstPtr<T>)reinterpret_cast<uintptr_t>(p);
+}
+// Launch metadata: an uploaded block (dev), or the kernel's own argument block, of which a LaunchMeta
+// is the first parameter (offset 0 of the kernel-argument segment).
+template <typename T>
+__device__ __forceinline__ ConstPtr<T> meta_at(const void* dev, uint32_t off) {
+  const auto base = dev ? (ConstPtr<char>)reinterpret_cast<uintptr_t>(dev)
+                        : (ConstPtr<char>)__builtin_amdgcn_kernarg_segment_ptr();
+  return (ConstPtr<T>)(base + off);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 }  // namespace cs

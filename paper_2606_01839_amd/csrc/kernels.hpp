@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstring>
+
 #include "host/host_state.hpp"
 
 namespace cs {
@@ -18,35 +20,72 @@ struct PoolGeom {
   int max_pages;
 };
 
-// KV append / unpack: write chunks (see PageChunk) of k,v [n_layers][src_rows][Hkv][D].
-hipError_t launch_append(const PoolGeom& g, const PageChunk* d_chunks, int n_chunks, const void* k,
-                         const void* v, int64_t src_rows, hipStream_t stream);
+// Metadata of one launch (descriptors, work lists, page ids): `bytes` bytes laid out on the host at
+// `host`, or already on the device at `dev` (a stream-ordered upload; `host` is then unused). A plan
+// of at most kMetaBytes travels in the launch's own kernel arguments (dev = nullptr): an upload is a
+// copy kernel of 2-5 us that the launch waits for (~8 us apart when nothing else is queued). Decode of
+// 16 conversations of 1k-9k tokens 29.4 -> 25.6 us, one of 24k 25.6 -> 23.3, prefill of 1.4k tokens
+// 39.4 -> 37.3; the larger argument block costs a launch of 690 us nothing measurable. Larger plans
+// are uploaded: they belong to launches of many tiles. 3 KiB keeps every kernel's arguments inside
+// the 4 KiB a launch may pass.
+constexpr size_t kMetaBytes = 3072;
+struct LaunchMeta {
+  alignas(16) uint32_t w[kMetaBytes / 4];
+};
+struct Meta {
+  const void* host = nullptr;
+  const void* dev = nullptr;
+  size_t bytes = 0;
+  // false: neither uploaded nor small enough to travel with the launch
+  bool ok() const { return dev != nullptr || (host != nullptr && bytes <= kMetaBytes); }
+};
+
+// The argument block of a launch whose plan is not on the device: the plan's bytes. (The rest of the
+// block is not read.)
+inline void fill_meta(const Meta& m, LaunchMeta* out) {
+  if (m.dev == nullptr) std::memcpy(out->w, m.host, m.bytes);
+}
+
+// KV append: write chunks (meta: PageChunk[n_chunks]) of k,v [n_layers][src_rows][Hkv][D]. With
+// carry_bytes > 0 the metadata travels in the kernel arguments and its bytes [carry_off, carry_off +
+// carry_bytes) (multiples of 16) are also stored to carry_dst, for the launches that follow.
+struct AppendCarry {
+  void* dst = nullptr;
+  size_t off = 0, bytes = 0;
+};
+hipError_t launch_append(const PoolGeom& g, const Meta& meta, int n_chunks, const AppendCarry& carry,
+                         const void* k, const void* v, int64_t src_rows, hipStream_t stream);
 
 // Pack: conversation pages (page-table row `slot`) -> wire [layer][lpage][head] blocks.
 hipError_t launch_pack(const PoolGeom& g, int slot, int64_t len, void* wire, hipStream_t stream);
 
-// Unpack: wire logical pages [lp0, lp0 + n_lp) -> physical pages d_pages[0..n_lp) of the
+// Unpack: wire logical pages [lp0, lp0 + n_lp) -> physical pages (meta: int32[n_lp]) of the
 // conversation in page-table row `slot` (length len).
-hipError_t launch_unpack(const PoolGeom& g, const void* wire, const int32_t* d_pages, int slot,
+hipError_t launch_unpack(const PoolGeom& g, const void* wire, const Meta& meta, int slot,
                          int64_t len, int lp0, int n_lp, hipStream_t stream);
 
 // Decode partial record of one (work item, query head): o[d], running max m, sum l, two unused
 // floats, so records stay 16-byte aligned.
 constexpr int partial_floats(int head_dim) { return head_dim + 4; }
 
-// Decode: split kernel over plan items (partials), then the merge kernel (output). d_order: the
-// plan's launch order of its n_items items (a permutation).
+// A decode plan as the kernels read it: meta = DecodeConvDesc[n_convs], then (16-byte aligned, at
+// order_off) the launch order of its n_items items (a permutation).
+struct DecodeLaunch {
+  Meta meta;
+  size_t order_off = 0;
+  int n_convs = 0, n_items = 0, split = 0;
+};
+
+// Decode: split kernel over plan items (partials), then the merge kernel (output).
 // direct_out != nullptr (only when every conversation is one item, n_items == n_convs): the split
 // writes the final output there and no merge follows.
-hipError_t launch_decode_split(const PoolGeom& g, int layer, const DecodeConvDesc* d_convs,
-                               const int32_t* d_order, int n_convs, int n_items, int split_tokens, const void* q,
+hipError_t launch_decode_split(const PoolGeom& g, int layer, const DecodeLaunch& w, const void* q,
                                float* partials, void* direct_out, hipStream_t stream);
-hipError_t launch_decode_merge(const PoolGeom& g, const DecodeConvDesc* d_convs, int n_convs,
-                               const float* partials, void* out, hipStream_t stream);
+hipError_t launch_decode_merge(const PoolGeom& g, const DecodeLaunch& w, const float* partials, void* out,
+                               hipStream_t stream);
 // Merge of layer l (merge_partials -> merge_out) and split of layer split_layer (-> split_partials,
 // a different buffer) in one launch; the same conversations and plan for both.
-hipError_t launch_decode_merge_split(const PoolGeom& g, int split_layer, const DecodeConvDesc* d_convs,
-                                     const int32_t* d_order, int n_convs, int n_items, int split_tokens, const void* q,
+hipError_t launch_decode_merge_split(const PoolGeom& g, int split_layer, const DecodeLaunch& w, const void* q,
                                      float* split_partials, const float* merge_partials,
                                      void* merge_out, hipStream_t stream);
 
@@ -61,13 +100,18 @@ constexpr size_t kStaticScratchFloats = size_t(4) << 20;
 // with hipGetSymbolAddress and cached; allocates nothing).
 hipError_t static_decode_scratch(float** out);
 
+// An extend plan as the kernels read it: meta = ExtendConvDesc[..], then (16-byte aligned, at
+// tiles_off) ExtendTile[n_tiles].
+struct ExtendLaunch {
+  Meta meta;
+  size_t tiles_off = 0;
+  int n_tiles = 0;
+};
+
 // One layer of a mixed step in one launch (head_dim 128 only): the extend tiles of the layer and
-// its decode split (partials; the merge follows as launch_decode_merge).
-hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendConvDesc* d_ext_convs,
-                              const ExtendTile* d_tiles, int n_tiles, const void* q_ext,
-                              void* out_ext, const DecodeConvDesc* d_dec_convs,
-                              const int32_t* d_dec_order, int n_dec_convs,
-                              int n_items, int split_tokens, const void* q_dec, float* partials,
+// its decode split (partials; the merge follows as launch_decode_merge). Both plans uploaded.
+hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q_ext,
+                              void* out_ext, const DecodeLaunch& w, const void* q_dec, float* partials,
                               void* direct_out, hipStream_t stream);
 
 // Query tokens per extend/prefill work tile for this head size and GQA group (the host plan must
@@ -75,8 +119,7 @@ hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendConvDesc
 int extend_query_tile(int head_dim, int group);
 
 // Extend / prefill: one workgroup per (tile, kv head).
-hipError_t launch_extend(const PoolGeom& g, int layer, const ExtendConvDesc* d_convs,
-                         const ExtendTile* d_tiles, int n_tiles, const void* q, void* out,
+hipError_t launch_extend(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q, void* out,
                          hipStream_t stream);
 
 }  // namespace cs

@@ -20,8 +20,9 @@ namespace cs {
 constexpr int kAppendChunks = 2;
 
 template <int D>
-__global__ __launch_bounds__(256) void kv_append_kernel(const PageChunk* __restrict__ chunks,
-                                                       int n_chunks,
+__global__ __launch_bounds__(256) void kv_append_kernel(LaunchMeta, const void* meta, int n_chunks,
+                                                       uint4* __restrict__ carry_dst, int carry_off,
+                                                       int carry_n16,
                                                        const uint16_t* __restrict__ k_src,
                                                        const uint16_t* __restrict__ v_src,
                                                        int64_t src_rows, uint16_t* __restrict__ pool,
@@ -41,6 +42,15 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const PageChunk* __restr
   const int lane = threadIdx.x & 63;
   const int ch = lane % kChunksPerRow;
 
+  if (carry_n16 > 0 && blockIdx.x == 0 && blockIdx.y == 0) {
+    const auto* src = meta_at<u32x4_t>(nullptr, carry_off);
+    for (int i = threadIdx.x; i < carry_n16; i += blockDim.x) {
+      const u32x4_t x = src[i];
+      carry_dst[i] = make_uint4(x.x, x.y, x.z, x.w);
+    }
+  }
+
+  const auto* chunks = meta_at<PageChunk>(meta, 0);
   PageChunk c[CH];
   bool have[CH];
   uint4 kv[CH][kPasses], vv[CH][kPasses];
@@ -48,7 +58,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const PageChunk* __restr
   for (int i = 0; i < CH; ++i) {
     const int idx = blockIdx.x * CH + i;
     have[i] = idx < n_chunks;
-    c[i] = chunks[have[i] ? idx : 0];
+    const auto* pc = chunks + (have[i] ? idx : 0);
+    c[i] = {pc->conv, pc->slot, pc->lpage, pc->page, pc->t0, pc->t1, pc->src_row, pc->new_page};
 #pragma unroll
     for (int ps = 0; ps < kPasses; ++ps) {
       const int t = lane / kChunksPerRow + ps * kRowsPerPass;
@@ -149,8 +160,8 @@ __global__ __launch_bounds__(64) void kv_pack_kernel(const uint16_t* __restrict_
 // Unpack: inverse of pack into pages d_pages[lp]; also fills the page-table mirror row.
 // ---------------------------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(64) void kv_unpack_kernel(const uint16_t* __restrict__ wire,
-                                                       const int32_t* __restrict__ d_pages,
+__global__ __launch_bounds__(64) void kv_unpack_kernel(LaunchMeta, const uint16_t* __restrict__ wire,
+                                                       const void* meta,
                                                        int64_t len, uint16_t* __restrict__ pool,
                                                        int64_t n_pages, int n_kv_heads,
                                                        int32_t* __restrict__ pt_row, int n_lpages,
@@ -159,7 +170,7 @@ __global__ __launch_bounds__(64) void kv_unpack_kernel(const uint16_t* __restric
   constexpr int kPerLane = kChunks / 64;
   const int lp = lp0 + blockIdx.x;
   const int layer = blockIdx.y / n_kv_heads, head = blockIdx.y % n_kv_heads;
-  const int page = d_pages[blockIdx.x];
+  const int page = meta_at<int32_t>(meta, 0)[blockIdx.x];
   const uint16_t* src = wire + ((static_cast<size_t>(layer) * n_lpages + lp) * n_kv_heads + head) *
                                    static_cast<size_t>(2 * kPageTokens * D);
   uint16_t* dst = pool + block_elem<D>(layer, page, head, n_pages, n_kv_heads);
@@ -184,16 +195,23 @@ static hipError_t by_dim(int D, F&& f) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_append(const PoolGeom& g, const PageChunk* d_chunks, int n_chunks, const void* k,
-                         const void* v, int64_t src_rows, hipStream_t stream) {
+hipError_t launch_append(const PoolGeom& g, const Meta& meta, int n_chunks, const AppendCarry& carry,
+                         const void* k, const void* v, int64_t src_rows, hipStream_t stream) {
   if (n_chunks == 0) return hipSuccess;
+  if (!meta.ok() || meta.bytes < n_chunks * sizeof(PageChunk)) return hipErrorInvalidValue;
+  if (carry.bytes > 0 && (meta.dev != nullptr || carry.dst == nullptr || carry.off % 16 || carry.bytes % 16 ||
+                          carry.off + carry.bytes > meta.bytes))
+    return hipErrorInvalidValue;
+  LaunchMeta m;
+  fill_meta(meta, &m);
   return by_dim(g.head_dim, [&](auto dc) {
     constexpr int D = decltype(dc)::value;
     // kv heads per workgroup: 4, 2 or 1, whichever is the largest that divides n_kv_heads
     const int waves = g.n_kv_heads % 4 == 0 ? 4 : (g.n_kv_heads % 2 == 0 ? 2 : 1);
     dim3 grid((n_chunks + kAppendChunks - 1) / kAppendChunks, g.n_layers * (g.n_kv_heads / waves));
     kv_append_kernel<D><<<grid, 64 * waves, 0, stream>>>(
-        d_chunks, n_chunks, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), src_rows,
+        m, meta.dev, n_chunks, static_cast<uint4*>(carry.dst), static_cast<int>(carry.off),
+        static_cast<int>(carry.bytes / 16), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), src_rows,
         static_cast<uint16_t*>(g.pool), g.n_pages, g.n_kv_heads, g.page_table, g.max_pages);
     return hipGetLastError();
   });
@@ -213,15 +231,18 @@ hipError_t launch_pack(const PoolGeom& g, int slot, int64_t len, void* wire, hip
   });
 }
 
-hipError_t launch_unpack(const PoolGeom& g, const void* wire, const int32_t* d_pages, int slot,
+hipError_t launch_unpack(const PoolGeom& g, const void* wire, const Meta& meta, int slot,
                          int64_t len, int lp0, int n_lp, hipStream_t stream) {
   const int n_lpages = static_cast<int>(pages_for(len));
   if (n_lp == 0) return hipSuccess;
+  if (!meta.ok() || meta.bytes < n_lp * sizeof(int32_t)) return hipErrorInvalidValue;
+  LaunchMeta m;
+  fill_meta(meta, &m);
   return by_dim(g.head_dim, [&](auto dc) {
     constexpr int D = decltype(dc)::value;
     dim3 grid(n_lp, g.n_layers * g.n_kv_heads);
     kv_unpack_kernel<D><<<grid, 64, 0, stream>>>(
-        static_cast<const uint16_t*>(wire), d_pages, len, static_cast<uint16_t*>(g.pool),
+        m, static_cast<const uint16_t*>(wire), meta.dev, len, static_cast<uint16_t*>(g.pool),
         g.n_pages, g.n_kv_heads, g.page_table + static_cast<size_t>(slot) * g.max_pages, n_lpages,
         lp0);
     return hipGetLastError();
