@@ -82,7 +82,8 @@ typedef struct {
  */
 size_t cs_pool_kv_bytes(const cs_pool_desc* desc);
 
-/* Device workspace bytes the pool needs (page-table mirror, decode partials, metadata ring). */
+/* Device workspace bytes the pool needs (page-table mirror, decode partials, records of extend tiles
+ * whose keys are cut into pieces, metadata ring). */
 size_t cs_pool_workspace_bytes(const cs_pool_desc* desc);
 
 /*
@@ -204,14 +205,13 @@ cs_status cs_attn_decode_batch_noalloc(cs_pool* pool, int32_t n_convs, const cs_
  * present, the extend launches run on a second stream owned by the pool, forked from `stream`
  * after the append and joined back into it before the call returns: work enqueued on `stream`
  * afterwards (and a synchronisation of `stream`) sees every output of the step.
- * flags = 0: every layer's queries are inputs of the call, so no layer waits for another; the
- *   extend work of all layers overlaps the decode work of all layers, and the decode merge of
- *   layer l-1 shares one launch with the decode split of layer l (two partial buffers alternate).
+ * flags = 0: every layer's queries are inputs of the call, so no layer waits for another: the extend
+ *   work of all layers is one launch and the decode work of all layers another (several where the
+ *   workspace has no room for the records of all layers), beside each other, each followed by its merge.
  * flags = CS_MIXED_LAYER_ORDERED: the order of a model forward pass, where layer l+1's queries
  *   depend on layer l's output: layer l's extend and decode overlap each other, and layer l+1
- *   starts only when both are complete. At head_dim 128 with both parts present, a layer is one
- *   launch holding its extend tiles and its decode split, then the decode merge; otherwise the
- *   layer's extend runs on the second stream beside its decode.
+ *   starts only when both are complete. With both parts present a layer is one launch holding its
+ *   extend tiles and its decode split, then one that merges what they left in pieces.
  * Outputs are bitwise the same either way (and the same as the separate calls).
  * Errors: as cs_kv_append_batch, cs_attn_extend and cs_attn_decode_batch; CS_EINVAL for unknown
  * flags.
@@ -255,9 +255,8 @@ cs_status cs_kv_unpack(cs_pool* pool, const void* src, size_t src_bytes, int64_t
 /*
  * Instrumentation (per-kernel timing; not part of the attention path). Between cs_profile_start
  * and cs_profile_stop every kernel the pool launches is bracketed by two HIP timing events on its
- * stream, except in cs_mixed_step, where one pair of events brackets the extend launches of all
- * layers and one pair the decode launches of all layers but the final merge (their time then
- * includes the gaps between those launches). cs_profile_stop waits for the events, writes the
+ * stream, except that in cs_mixed_step one pair of events brackets the extend launches of all layers
+ * (their time then includes the gaps between those launches). cs_profile_stop waits for the events, writes the
  * summed milliseconds and the launch count per kernel kind into ms[CS_PROF_KINDS] and
  * launches[CS_PROF_KINDS], and disables timing.
  * Errors: CS_EINVAL (null), CS_EHIP.
@@ -267,8 +266,8 @@ enum {
   CS_PROF_PACK = 1,          /* kv pack kernel */
   CS_PROF_UNPACK = 2,        /* kv unpack kernel */
   CS_PROF_DECODE_SPLIT = 3,  /* decode split-K kernel */
-  CS_PROF_DECODE_MERGE = 4,  /* decode merge kernel */
-  CS_PROF_ATTN_FWD = 5,      /* prefill / extend attention kernel */
+  CS_PROF_DECODE_MERGE = 4,  /* decode merge kernel; in a layer-ordered mixed step also the extend merge */
+  CS_PROF_ATTN_FWD = 5,      /* prefill / extend attention kernel and the merge of cut tiles */
   CS_PROF_MIXED_LAYER = 6,   /* one layer's extend tiles + decode split in one launch */
   CS_PROF_KINDS = 7
 };

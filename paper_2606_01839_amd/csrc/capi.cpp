@@ -34,9 +34,13 @@ constexpr int64_t kDecodeTargetItems = 4096;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+constexpr int kMaxLayersPerLaunch = 32768;  // a grid dimension
+// Records of cut extend tiles one launch may write: two per CU (68 MB of workspace at head dim 128).
+constexpr int kExtendRecords = 2 * cs::kCus;
+
 struct WsLayout {
-  size_t page_table, partials, partials2, ring, total;
-  size_t partial_floats;
+  size_t page_table, partials, ext_parts, ring, total;
+  size_t partial_floats;  // decode records: at least one layer of any batch, two in a multi-layer pool
 };
 
 int64_t max_decode_items(const cs_pool_desc& d) {
@@ -46,17 +50,16 @@ int64_t max_decode_items(const cs_pool_desc& d) {
 
 WsLayout ws_layout(const cs_pool_desc& d) {
   WsLayout w{};
-  const int group = d.n_q_heads / d.n_kv_heads;
   w.page_table = 0;
   size_t pt_bytes = static_cast<size_t>(d.max_convs) * static_cast<size_t>(d.max_pages_per_conv) * 4;
   w.partials = align_up(pt_bytes, kAlign);
-  w.partial_floats =
-      static_cast<size_t>(max_decode_items(d)) * d.n_kv_heads * group * cs::partial_floats(d.head_dim);
-  // A multi-layer pool gets a second partial buffer: cs_mixed_step merges layer l while it splits
-  // layer l+1 in the same launch.
-  w.partials2 = align_up(w.partials + w.partial_floats * 4, kAlign);
-  const size_t second = d.n_layers > 1 ? w.partial_floats * 4 : 0;
-  w.ring = align_up(w.partials2 + second, kAlign);
+  w.partial_floats = static_cast<size_t>(max_decode_items(d)) * d.n_q_heads * cs::partial_floats(d.head_dim) *
+                     (d.n_layers > 1 ? 2 : 1);
+  w.ext_parts = align_up(w.partials + w.partial_floats * 4, kAlign);
+  // a pool whose longest conversation is too short to be cut needs no records
+  const int64_t longest = std::min<int64_t>(d.max_pages_per_conv, d.n_pages) * cs::kPage;
+  const size_t records = longest > cs::kExtendKeyTile * cs::kMinPiece ? kExtendRecords : 0;
+  w.ring = align_up(w.ext_parts + records * cs::extend_part_floats(d.head_dim) * 4, kAlign);
   w.total = w.ring + kRingBytes;
   return w;
 }
@@ -136,7 +139,7 @@ struct cs_pool {
     return g;
   }
   float* partials() const { return reinterpret_cast<float*>(ws + lay.partials); }
-  float* partials2() const { return reinterpret_cast<float*>(ws + lay.partials2); }
+  float* ext_parts() const { return reinterpret_cast<float*>(ws + lay.ext_parts); }
 };
 
 namespace {
@@ -384,8 +387,10 @@ struct ExtendWork {
 
 cs::ExtendPlan plan_extend_batch(const cs_pool* p, const std::vector<int32_t>& slots,
                                  const std::vector<int64_t>& lens, const std::vector<int32_t>& q_lens) {
-  const int tile = cs::extend_query_tile(p->desc.head_dim, p->desc.n_q_heads / p->desc.n_kv_heads);
-  return cs::plan_extend(slots, lens, q_lens, tile);
+  const int tile = cs::extend_query_tile(p->desc.n_q_heads / p->desc.n_kv_heads);
+  cs::ExtendPlan plan = cs::plan_extend(slots, lens, q_lens, tile);
+  cs::split_extend(plan, p->desc.n_kv_heads, cs::kCus, kExtendRecords);
+  return plan;
 }
 
 // Tiles [t0, t1) of a plan with its conversations, laid out at the end of the block; offsets of
@@ -394,7 +399,12 @@ cs::ExtendLaunch push_extend(const cs::ExtendPlan& plan, size_t t0, size_t t1, B
   cs::ExtendLaunch e;
   *off = b->push(plan.convs.data(), plan.convs.size());
   e.tiles_off = b->push(plan.tiles.data() + t0, t1 - t0) - *off;
+  e.merges_off = b->push(plan.merges.data(), plan.merges.size()) - *off;
   e.n_tiles = static_cast<int>(t1 - t0);
+  e.n_merges = static_cast<int>(plan.merges.size());
+  e.piece = plan.piece;
+  e.n_parts = plan.n_parts;
+  e.q_rows = plan.convs.empty() ? 0 : plan.convs.back().q_row + plan.convs.back().q_len;
   return e;
 }
 
@@ -402,6 +412,7 @@ cs_status upload_extend(cs_pool* p, const cs::ExtendPlan& plan, ExtendWork* w) {
   const size_t desc_bytes = align_up(plan.convs.size() * sizeof(cs::ExtendConvDesc), 16);
   if (desc_bytes + kAlign + sizeof(cs::ExtendTile) > kQuarter)
     return fail(CS_ENOMEM, "batch descriptor exceeds the metadata ring");
+  // (a plan with cut tiles is small: it stays in one part)
   const size_t max_tiles = (kQuarter - desc_bytes - kAlign) / sizeof(cs::ExtendTile);
   for (size_t t0 = 0; t0 < plan.tiles.size(); t0 += max_tiles) {
     Blob b;
@@ -415,13 +426,27 @@ cs_status upload_extend(cs_pool* p, const cs::ExtendPlan& plan, ExtendWork* w) {
   return CS_OK;
 }
 
-cs_status launch_extend_layer(cs_pool* p, const ExtendWork& w, int layer, const void* q, void* out,
-                              hipStream_t s) {
+// Layers [0, n_layers) of a step from `layer` on; q and out hold them one after the other. The layers
+// of one launch are as many as the records of their cut tiles have room for.
+cs_status launch_extend_layers(cs_pool* p, const ExtendWork& w, int layer, int n_layers, const void* q, void* out,
+                               hipStream_t s) {
   const cs::PoolGeom g = p->geom();
+  const size_t row_bytes = static_cast<size_t>(g.n_q_heads) * g.head_dim * 2;
   for (const auto& e : w.parts) {
-    cs_status st = timed_launch_on(p, s, CS_PROF_ATTN_FWD, "attention launch",
-                                   [&] { return cs::launch_extend(g, layer, e, q, out, s); });
-    if (st != CS_OK) return st;
+    const int per = std::min(kMaxLayersPerLaunch,
+                             e.n_parts == 0 ? n_layers : std::max(1, kExtendRecords / (e.n_parts * g.n_kv_heads)));
+    for (int l = 0; l < n_layers; l += per) {
+      const int nl = std::min(per, n_layers - l);
+      const char* ql = static_cast<const char*>(q) + l * e.q_rows * row_bytes;
+      char* ol = static_cast<char*>(out) + l * e.q_rows * row_bytes;
+      cs_status st = timed_launch_on(p, s, CS_PROF_ATTN_FWD, "attention launch", [&] {
+        return cs::launch_extend(g, layer + l, nl, e, ql, ol, p->ext_parts(), s);
+      });
+      if (st == CS_OK && e.n_merges > 0)
+        st = timed_launch_on(p, s, CS_PROF_ATTN_FWD, "attention merge launch",
+                             [&] { return cs::launch_extend_merge(g, nl, e, ol, p->ext_parts(), s); });
+      if (st != CS_OK) return st;
+    }
   }
   return CS_OK;
 }
@@ -466,16 +491,28 @@ cs_status place_decode(cs_pool* p, const cs::DecodePlan& plan, DecodeWork* dw) {
   return place_meta(p, dw->blob, &dw->w.meta);
 }
 
-// Split, then merge; when every conversation is one work item the split writes the output itself.
-cs_status launch_decode_layer(cs_pool* p, const DecodeWork& w, int layer, const void* q, void* out) {
+// Split, then merge, of n_layers layers from `layer` on (q and out hold them one after the other); when
+// every conversation is one work item the split writes the output itself. The layers of one launch
+// are as many as their records have room for.
+cs_status launch_decode_layers(cs_pool* p, const DecodeWork& w, int layer, int n_layers, const void* q, void* out) {
   const cs::PoolGeom g = p->geom();
-  cs_status st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
-    return cs::launch_decode_split(g, layer, w.w, q, p->partials(), w.single ? out : nullptr, p->stream);
-  });
-  if (st != CS_OK || w.single) return st;
-  return timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch", [&] {
-    return cs::launch_decode_merge(g, w.w, p->partials(), out, p->stream);
-  });
+  const size_t row_bytes = static_cast<size_t>(g.n_q_heads) * g.head_dim * 2;
+  const size_t records = static_cast<size_t>(w.w.n_items) * g.n_q_heads * cs::partial_floats(g.head_dim);
+  const int room = static_cast<int>(std::min<size_t>(kMaxLayersPerLaunch, p->lay.partial_floats / records));
+  const int per = w.single ? kMaxLayersPerLaunch : room;   // room >= 1: check_decode_plan
+  for (int l = 0; l < n_layers; l += per) {
+    const int nl = std::min(per, n_layers - l);
+    const char* ql = static_cast<const char*>(q) + l * w.w.n_convs * row_bytes;
+    char* ol = static_cast<char*>(out) + l * w.w.n_convs * row_bytes;
+    cs_status st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
+      return cs::launch_decode_split(g, layer + l, nl, w.w, ql, p->partials(), w.single ? ol : nullptr, p->stream);
+    });
+    if (st == CS_OK && !w.single)
+      st = timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch",
+                        [&] { return cs::launch_decode_merge(g, nl, w.w, p->partials(), ol, p->stream); });
+    if (st != CS_OK) return st;
+  }
+  return CS_OK;
 }
 
 cs_status attend(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t* q_lens, int32_t layer,
@@ -510,7 +547,7 @@ cs_status attend(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t* q_l
   }
   ExtendWork w;
   if ((st = upload_extend(p, plan_extend_batch(p, slots, lens, ql), &w)) != CS_OK) return st;
-  return launch_extend_layer(p, w, layer, q, out, p->stream);
+  return launch_extend_layers(p, w, layer, 1, q, out, p->stream);
 }
 
 // Whether the conversations can take n_new[i] tokens each (nothing is changed); *total = their sum.
@@ -764,7 +801,7 @@ cs_status cs_attn_decode_batch(cs_pool* p, int32_t n, const cs_conv* convs, int3
   if ((st = check_decode_plan(p, plan)) != CS_OK) return st;
   DecodeWork w;
   if ((st = place_decode(p, plan, &w)) != CS_OK) return st;
-  return launch_decode_layer(p, w, layer, q, out);
+  return launch_decode_layers(p, w, layer, 1, q, out);
 }
 
 cs_status cs_attn_decode_batch_noalloc(cs_pool* p, int32_t n, const cs_conv* convs, int32_t layer,
@@ -804,10 +841,10 @@ cs_status cs_attn_decode_batch_noalloc(cs_pool* p, int32_t n, const cs_conv* con
   if ((st = place_decode(p, plan, &w)) != CS_OK) return st;
   const cs::PoolGeom g = p->geom();
   // untimed launches: the timing events of cs_profile_* would be created on demand
-  CS_HIP(cs::launch_decode_split(g, layer, w.w, q, scratch, w.single ? out : nullptr, p->stream),
+  CS_HIP(cs::launch_decode_split(g, layer, 1, w.w, q, scratch, w.single ? out : nullptr, p->stream),
          "decode split launch");
   if (w.single) return CS_OK;
-  CS_HIP(cs::launch_decode_merge(g, w.w, scratch, out, p->stream), "decode merge launch");
+  CS_HIP(cs::launch_decode_merge(g, 1, w.w, scratch, out, p->stream), "decode merge launch");
   return CS_OK;
 }
 
@@ -935,7 +972,8 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
   const size_t d_bytes = blob.bytes.size();
   // an extend plan that does not fit beside the decode plan is uploaded by itself, maybe in parts
   const bool e_carried = n_ext > 0 && d_bytes + e_plan.convs.size() * sizeof(cs::ExtendConvDesc) +
-                                              e_plan.tiles.size() * sizeof(cs::ExtendTile) + 64 <= kQuarter;
+                                              e_plan.tiles.size() * sizeof(cs::ExtendTile) +
+                                              e_plan.merges.size() * sizeof(cs::ExtendMerge) + 64 <= kQuarter;
   if (e_carried) ew.parts.push_back(push_extend(e_plan, 0, e_plan.tiles.size(), &blob, &e_off));
   // append every new token (all layers); validates capacity and commits the host metadata
   void* dev = nullptr;
@@ -958,8 +996,7 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
   // returns), so the matrix-core-bound extend work overlaps the HBM-bound decode work.
   const bool fork = n_ext > 0 && n_dec > 0;
   // layer order with one launch per layer (extend tiles + decode split) needs no second stream
-  const bool fused_layers = (flags & CS_MIXED_LAYER_ORDERED) && fork && p->desc.head_dim == 128 &&
-                            ew.parts.size() == 1;
+  const bool fused_layers = (flags & CS_MIXED_LAYER_ORDERED) && fork && ew.parts.size() == 1;
   hipStream_t ext_stream = p->stream;
   if (fork && !fused_layers && (st = ensure_side(p)) != CS_OK) return st;
   if (fork && !fused_layers) ext_stream = p->side;
@@ -975,16 +1012,18 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
   };
   if (fused_layers) {
     // As in a model forward pass, one layer after the other; each layer is one launch with its
-    // extend tiles and its decode split, then the decode merge.
+    // extend tiles and its decode split, then one that merges what they left in pieces.
     const cs::PoolGeom g = p->geom();
+    const auto& e = ew.parts[0];
     for (int layer = 0; layer < nl && st == CS_OK; ++layer) {
       st = timed_launch(p, CS_PROF_MIXED_LAYER, "mixed layer launch", [&] {
-        return cs::launch_mixed_layer(g, layer, ew.parts[0], q_e(layer), o_e(layer), dw.w, q_d(layer), p->partials(),
-                                      dw.single ? o_d(layer) : nullptr, p->stream);
+        return cs::launch_mixed_layer(g, layer, e, q_e(layer), o_e(layer), p->ext_parts(), dw.w, q_d(layer),
+                                      p->partials(), dw.single ? o_d(layer) : nullptr, p->stream);
       });
-      if (st == CS_OK && !dw.single)
-        st = timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch", [&] {
-          return cs::launch_decode_merge(g, dw.w, p->partials(), o_d(layer), p->stream);
+      if (st == CS_OK && (e.n_merges > 0 || !dw.single))
+        st = timed_launch(p, CS_PROF_DECODE_MERGE, "mixed merge launch", [&] {
+          return cs::launch_mixed_merge(g, e, o_e(layer), p->ext_parts(), dw.w, p->partials(),
+                                        dw.single ? nullptr : o_d(layer), p->stream);
         });
     }
     return st;
@@ -994,8 +1033,8 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     // starts only once both are complete.
     for (int layer = 0; layer < nl && st == CS_OK; ++layer) {
       if (fork && (st = fork_side()) != CS_OK) return st;
-      if (n_ext > 0) st = launch_extend_layer(p, ew, layer, q_e(layer), o_e(layer), ext_stream);
-      if (n_dec > 0 && st == CS_OK) st = launch_decode_layer(p, dw, layer, q_d(layer), o_d(layer));
+      if (n_ext > 0) st = launch_extend_layers(p, ew, layer, 1, q_e(layer), o_e(layer), ext_stream);
+      if (n_dec > 0 && st == CS_OK) st = launch_decode_layers(p, dw, layer, 1, q_d(layer), o_d(layer));
       if (fork) {  // join even after a failed launch, so later work never overtakes the side stream
         const cs_status sj = join_side();
         if (st == CS_OK) st = sj;
@@ -1003,43 +1042,15 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     }
     return st;
   }
-  // Every layer's queries are inputs of this call, so no layer waits for another: the extend
-  // launches of all layers run on the side stream while the main stream decodes all layers.
+  // Every layer's queries are inputs of this call, so no layer waits for another: one launch takes the
+  // extend tiles of all layers on the side stream while one on the main stream decodes all layers
+  // (each followed by its merge). Against a launch per layer this leaves no half-empty last round and
+  // no gap per layer.
   if (fork && (st = fork_side()) != CS_OK) return st;
   if (n_ext > 0) st = span_begin(p, ext_stream, CS_PROF_ATTN_FWD);
-  for (int layer = 0; layer < nl && n_ext > 0 && st == CS_OK; ++layer)
-    st = launch_extend_layer(p, ew, layer, q_e(layer), o_e(layer), ext_stream);
+  if (n_ext > 0 && st == CS_OK) st = launch_extend_layers(p, ew, 0, nl, q_e(0), o_e(0), ext_stream);
   if (const cs_status se = span_end(p); st == CS_OK) st = se;
-  // Decode of all layers, one launch per layer: with one work item per conversation each layer's
-  // split writes its output; otherwise split(0), then for l >= 1 a launch that merges layer l-1
-  // and splits layer l into the other partial buffer, and finally merge(last).
-  if (n_dec > 0 && st == CS_OK && dw.single) {
-    const cs::PoolGeom g = p->geom();
-    st = span_begin(p, p->stream, CS_PROF_DECODE_SPLIT);
-    for (int layer = 0; layer < nl && st == CS_OK; ++layer)
-      st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
-        return cs::launch_decode_split(g, layer, dw.w, q_d(layer), p->partials(), o_d(layer), p->stream);
-      });
-    if (const cs_status se = span_end(p); st == CS_OK) st = se;
-  } else if (n_dec > 0 && st == CS_OK) {
-    const cs::PoolGeom g = p->geom();
-    float* buf[2] = {p->partials(), p->partials2()};
-    st = span_begin(p, p->stream, CS_PROF_DECODE_SPLIT);
-    if (st == CS_OK) st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode split launch", [&] {
-      return cs::launch_decode_split(g, 0, dw.w, q_d(0), buf[0], nullptr, p->stream);
-    });
-    for (int layer = 1; layer < nl && st == CS_OK; ++layer) {
-      st = timed_launch(p, CS_PROF_DECODE_SPLIT, "decode merge+split launch", [&] {
-        return cs::launch_decode_merge_split(g, layer, dw.w, q_d(layer), buf[layer % 2], buf[(layer - 1) % 2],
-                                             o_d(layer - 1), p->stream);
-      });
-    }
-    if (const cs_status se = span_end(p); st == CS_OK) st = se;
-    if (st == CS_OK)
-      st = timed_launch(p, CS_PROF_DECODE_MERGE, "decode merge launch", [&] {
-        return cs::launch_decode_merge(g, dw.w, buf[(nl - 1) % 2], o_d(nl - 1), p->stream);
-      });
-  }
+  if (n_dec > 0 && st == CS_OK) st = launch_decode_layers(p, dw, 0, nl, q_d(0), o_d(0));
   if (fork) {  // join even after a failed launch, so later work never overtakes the side stream
     const cs_status sj = join_side();
     if (st == CS_OK) st = sj;

@@ -1,5 +1,5 @@
-// Split phase of batched decode (split-K flash decoding over paged KV), shared by the decode
-// kernels and by the fused extend + decode kernel of a mixed step; see decode.hip.
+// Split and merge phases of batched decode (split-K flash decoding over paged KV), shared by the
+// decode kernels and by the fused extend + decode kernels of a mixed step; see decode.hip.
 #pragma once
 
 #include <cmath>
@@ -58,6 +58,7 @@ constexpr int kDecodeItemThreads = 64 * kDecodeSubSplits;
 template <int D>
 constexpr int split_exchange_floats() { return (kDecodeSubSplits - 1) * 8 * (D + 2); }
 
+// `dl` = layer of the launch, counted from a.layer.
 // Work unit `work` = (order[work / n_kv_heads], work % n_kv_heads) = (item, kv head) of the plan,
 // taken by one workgroup of kDecodeSubSplits waves (this wave = `wave`; `xch` = its LDS exchange
 // area, split_exchange_floats<D>() floats). The item's n keys are shared out evenly: wave w reads
@@ -69,7 +70,7 @@ constexpr int split_exchange_floats() { return (kDecodeSubSplits - 1) * 8 * (D +
 // waves per item than with one). Every wave reaches the one barrier, also in a workgroup whose
 // work unit lies past the end (work >= n_items * n_kv_heads: no keys, nothing written).
 template <int D>
-__device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, const int wave,
+__device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, const int dl, const int wave,
                                            float* xch) {
   constexpr int KS = D / 32;  // k-steps of the QK^T contraction
   constexpr int DT = D / 16;  // 16-dim tiles of the output
@@ -95,7 +96,7 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
   const int n_q_heads = a.n_kv_heads * a.group;
   bf16x8 qop[KS];
   {
-    const uint16_t* qrow = a.q + (static_cast<size_t>(conv_idx) * n_q_heads + g * a.group + c) * D;
+    const uint16_t* qrow = a.q + (static_cast<size_t>(dl * a.n_convs + conv_idx) * n_q_heads + g * a.group + c) * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       qop[ks] = c < a.group ? as_bf16x8(ld16(qrow + 32 * ks + 8 * qd)) : bf16x8{};
@@ -108,7 +109,7 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
   for (int t = 0; t < DT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const size_t head_stride = static_cast<size_t>(2 * kPageTokens * D);
-  const uint16_t* layer_base = a.pool + static_cast<size_t>(a.layer) * a.n_pages * a.n_kv_heads * head_stride +
+  const uint16_t* layer_base = a.pool + static_cast<size_t>(a.layer + dl) * a.n_pages * a.n_kv_heads * head_stride +
                                static_cast<size_t>(g) * head_stride;
   const size_t page_stride = static_cast<size_t>(a.n_kv_heads) * head_stride;
   // Per-lane byte offsets inside a page block (the same for every page): key c, dims 8 qd ..
@@ -226,7 +227,7 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
         for (int r = 0; r < 4; ++r) o[t][r] = __builtin_fmaf(aw, x[16 * t + 4 * qd + r], o[t][r]);
     }
     if (a.direct) {  // the item is the whole conversation: out = o / l (as the merge computes it)
-      uint16_t* orow = a.out + (static_cast<size_t>(conv_idx) * a.n_kv_heads * a.group + g * a.group + c) * D;
+      uint16_t* orow = a.out + (static_cast<size_t>(dl * a.n_convs + conv_idx) * a.n_kv_heads * a.group + g * a.group + c) * D;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
         st8(orow + 16 * t + 4 * qd, make_uint2(pack_bf16x2(o[t][0] / l, o[t][1] / l),
@@ -234,13 +235,75 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
       return;
     }
     // non-temporal: the record is read once, by the merge (about 1% faster than plain stores)
-    float* pp = a.partials + ((static_cast<size_t>(item) * a.n_kv_heads + g) * a.group + c) * partial_floats(D);
+    float* pp = a.partials + ((static_cast<size_t>(dl * a.n_items + item) * a.n_kv_heads + g) * a.group + c) * partial_floats(D);
 #pragma unroll
     for (int t = 0; t < DT; ++t) __builtin_nontemporal_store(o[t], reinterpret_cast<f32x4*>(pp + 16 * t + 4 * qd));
     if (qd == 0) {
       pp[D] = M;
       pp[D + 1] = l;
     }
+  }
+}
+
+// Log-sum-exp merge of the item records of one (conversation b, query head h) by 256 threads (`tid`
+// in 0 .. 255, LDS `lds`), in three steps whose order depends only on the record count (bitwise
+// deterministic): the maximum M of the record maxima; per thread, the weighted sum over a fixed
+// subset of the records (group sg = tid / (D/4) takes records sg, sg + SG, ...; dim group = 4
+// consecutive dims, one 16-byte load); then the groups added in order 0 .. SG-1. `dl` = layer of the
+// launch.
+template <int D>
+struct MergeLds {
+  float red_o[256 / (D / 4)][D];
+  float red_l[256 / (D / 4)];
+  float wave_max[4];
+};
+
+template <int D>
+__device__ __forceinline__ void merge_body(const DecodeArgs& a, const int b, const int h, const int dl,
+                                           const int tid, MergeLds<D>& lds) {
+  constexpr int DV = D / 4;          // dim groups (4 dims each)
+  constexpr int SG = 256 / DV;       // record groups
+  constexpr int R = partial_floats(D);
+  const int g = h / a.group, c = h % a.group;
+  const DecodeConvDesc cd = load_desc(a.convs() + b);
+  const int lane = tid & 63, wave = tid >> 6;
+  const size_t split_stride = static_cast<size_t>(a.n_kv_heads) * a.group * R;
+  const float* base =
+      a.partials + dl * a.n_items * split_stride + ((static_cast<size_t>(cd.item_start) * a.n_kv_heads + g) * a.group + c) * R;
+  const int n = cd.n_splits;
+
+  float M = -INFINITY;
+  for (int s = tid; s < n; s += 256) M = fmaxf(M, base[s * split_stride + D]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, xor_shfl(M, off));
+  if (lane == 0) lds.wave_max[wave] = M;
+  __syncthreads();
+  M = fmaxf(fmaxf(lds.wave_max[0], lds.wave_max[1]), fmaxf(lds.wave_max[2], lds.wave_max[3]));
+
+  const int dg = tid % DV, sg = tid / DV;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float den = 0.f;
+#pragma unroll 4
+  for (int s = sg; s < n; s += SG) {
+    const float* p = base + s * split_stride;
+    const f32x2 ml = *reinterpret_cast<const f32x2*>(p + D);
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + 4 * dg);
+    const float w = fast_exp2(ml.x - M);
+    acc += w * v;
+    den += w * ml.y;
+  }
+  *reinterpret_cast<f32x4*>(&lds.red_o[sg][4 * dg]) = acc;
+  if (dg == 0) lds.red_l[sg] = den;
+  __syncthreads();
+  if (tid < D) {
+    float o = 0.f, l = 0.f;
+#pragma unroll
+    for (int k = 0; k < SG; ++k) {
+      o += lds.red_o[k][tid];
+      l += lds.red_l[k];
+    }
+    uint16_t* orow = a.out + (static_cast<size_t>(dl * a.n_convs + b) * a.n_kv_heads * a.group + h) * D;
+    orow[tid] = static_cast<uint16_t>(pack_bf16x2(o / l, 0.f) & 0xFFFFu);
   }
 }
 

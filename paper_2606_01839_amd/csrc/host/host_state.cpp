@@ -1,6 +1,7 @@
 #include "host_state.hpp"
 
 #include <algorithm>
+#include <functional>
 #include <numeric>
 
 namespace cs {
@@ -125,7 +126,7 @@ ExtendPlan plan_extend(const std::vector<int32_t>& slots, const std::vector<int6
     row += q_lens[i];
     for (int32_t q0 = 0; q0 < q_lens[i]; q0 += q_tile) {
       int64_t keys = lens[i] - q_lens[i] + std::min(q_lens[i], q0 + q_tile);
-      work.push_back({keys, {static_cast<int32_t>(i), q0}});
+      work.push_back({keys, {static_cast<int32_t>(i), q0, 0, -1}});
     }
   }
   // Conversation-major order: longest conversation first, its heaviest tiles first. Workgroups that
@@ -142,6 +143,99 @@ ExtendPlan plan_extend(const std::vector<int32_t>& slots, const std::vector<int6
   plan.tiles.reserve(work.size());
   for (auto& w : work) plan.tiles.push_back(w.second);
   return plan;
+}
+
+// The line between cutting and not cutting is an estimate of the launch's time, in steps of one key
+// tile (1.16 us at head dim 128 on a part-filled chip): the CUs one kv head gets (n_cus / n_kv_heads) take
+// the workgroups longest first; each costs its key tiles plus kStartSteps (measured 9 us: plan, pages,
+// queries and first tiles one after the other from memory, the refresh of the first tile's maximum, the
+// last stores), and cutting costs the merge launch plus the records' way to memory and back.
+constexpr float kStartSteps = 8.f;
+constexpr float kMergeSteps = 6.f;
+constexpr float kRecordSteps = 0.03f;
+
+// Time of workgroups of the given key tiles (longest first) on `slots` CUs.
+static float makespan(const std::vector<int32_t>& keys, int slots) {
+  if (keys.empty()) return 0.f;
+  if (static_cast<int>(keys.size()) <= slots) return static_cast<float>(keys[0]) + kStartSteps;
+  std::vector<float> end(static_cast<size_t>(slots), 0.f);  // min-heap of the CUs' end times
+  float last = 0.f;
+  for (int32_t k : keys) {
+    std::pop_heap(end.begin(), end.end(), std::greater<float>());
+    end.back() += static_cast<float>(k) + kStartSteps;
+    last = std::max(last, end.back());
+    std::push_heap(end.begin(), end.end(), std::greater<float>());
+  }
+  return last;
+}
+
+void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t max_records) {
+  const int n = static_cast<int>(plan.tiles.size());
+  const int slots = std::max(1, n_cus / n_kv_heads);
+  const int max_parts = max_records / n_kv_heads;
+  // Beyond two rounds of tiles cutting could win back only part of the last.
+  if (n == 0 || n > 2 * slots || max_parts < 2) return;
+  std::vector<int32_t> keys(static_cast<size_t>(n));
+  int64_t total = 0;
+  for (int i = 0; i < n; ++i) {
+    const ExtendConvDesc& c = plan.convs[static_cast<size_t>(plan.tiles[i].conv)];
+    const int32_t seen = c.len - c.q_len + std::min(c.q_len, plan.tiles[i].q0 + plan.q_tile);
+    keys[i] = (seen + kExtendKeyTile - 1) / kExtendKeyTile;
+    total += keys[i];
+  }
+  std::vector<int32_t> sorted = keys;
+  std::sort(sorted.begin(), sorted.end(), std::greater<int32_t>());
+  const int32_t longest = sorted[0];
+  if (longest <= kMinPiece) return;
+  float best = 0.9f * makespan(sorted, slots);  // cut only for a clear gain
+  int32_t best_c = 0;
+  std::vector<int32_t> work_keys;
+  for (int rounds = 1; rounds <= 4; ++rounds) {
+    // the smallest size whose pieces fit in this many rounds of the CUs, and their records
+    int32_t c = std::max<int32_t>(kMinPiece, static_cast<int32_t>(total / (static_cast<int64_t>(rounds) * slots)));
+    int pieces = 0, parts = 0;
+    for (;; c += std::max(1, c / 16)) {
+      pieces = parts = 0;
+      for (int32_t k : keys) {
+        const int np = (k + c - 1) / c;
+        pieces += np;
+        parts += np > 1 ? np : 0;
+      }
+      if (c >= longest || (pieces <= rounds * slots && parts <= max_parts)) break;
+    }
+    if (c >= longest) continue;
+    work_keys.clear();
+    for (int32_t k : keys) work_keys.insert(work_keys.end(), static_cast<size_t>(k / c), c);
+    for (int32_t k : keys)
+      if (k % c) work_keys.push_back(k % c);
+    std::sort(work_keys.begin(), work_keys.end(), std::greater<int32_t>());
+    const float t = makespan(work_keys, slots) + kMergeSteps + kRecordSteps * static_cast<float>(parts * n_kv_heads);
+    if (t < best) {
+      best = t;
+      best_c = c;
+    }
+  }
+  if (best_c == 0) return;
+  plan.piece = best_c;
+  std::vector<std::pair<int32_t, ExtendTile>> work;
+  for (int i = 0; i < n; ++i) {
+    ExtendTile t = plan.tiles[i];
+    if (keys[i] <= best_c) {
+      work.push_back({keys[i], t});
+      continue;
+    }
+    const int np = (keys[i] + best_c - 1) / best_c;
+    plan.merges.push_back({t.conv, t.q0, plan.n_parts, np});
+    for (int s = 0; s < np; ++s) {
+      t.k0 = s * best_c;
+      t.part = plan.n_parts++;
+      work.push_back({std::min(best_c, keys[i] - t.k0), t});
+    }
+  }
+  // longest first, so the last round holds the shortest
+  std::stable_sort(work.begin(), work.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  plan.tiles.clear();
+  for (auto& w : work) plan.tiles.push_back(w.second);
 }
 
 std::vector<PageChunk> plan_append(const std::vector<int32_t>& slots,

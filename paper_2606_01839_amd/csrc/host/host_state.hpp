@@ -11,6 +11,7 @@
 namespace cs {
 
 constexpr int kPage = 16;  // tokens per KV page
+constexpr int kCus = 256;  // compute units of the part, which the plans fill
 
 inline int64_t pages_for(int64_t tokens) { return (tokens + kPage - 1) / kPage; }
 
@@ -110,8 +111,8 @@ struct DecodePlan {
 DecodePlan plan_decode(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
                        int32_t n_kv_heads, int64_t target_items);
 
-// Extend / prefill: queries are the last q_len tokens of each conversation, tiled by 64 query
-// tokens; one tile = (conversation, 64-token query block) x one kv head.
+// Extend / prefill: queries are the last q_len tokens of each conversation, cut into tiles of q_tile
+// query tokens; one tile = (conversation, query block) x one kv head.
 struct ExtendConvDesc {
   int32_t slot;
   int32_t len;    // tokens (keys) of the conversation
@@ -119,19 +120,46 @@ struct ExtendConvDesc {
   int32_t q_row;  // first row of this conversation in the q/out tensors
 };
 
+constexpr int kExtendKeyTile = 64;  // keys per step of the attention kernel
+// Key tiles of the smallest piece; below, a piece is mostly start-up and records. One 64-token chunk on
+// 3000 tokens takes 22.1 us with 6, 24.1 with 8 (65 uncut), but a step of 8 conversations over 32 layers
+// 2134 / 2062 us and one of 4 over 28 layers in one launch 391 / 366, where other work fills the CUs.
+constexpr int kMinPiece = 8;
+
 struct ExtendTile {
-  int32_t conv;   // index into the batch
-  int32_t q0;     // first query index (0-based within the conversation's q_len)
+  int32_t conv;       // index into the batch
+  int32_t q0;         // first query index (0-based within the conversation's q_len)
+  int32_t k0 = 0;     // first key tile
+  int32_t part = -1;  // -1: every key tile the queries see; else piece `part` of the launch: key
+                      // tiles [k0, k0 + ExtendPlan::piece) of them
+};
+
+// The pieces part0 .. part0 + n_parts - 1 of a cut tile, in key order.
+struct ExtendMerge {
+  int32_t conv;
+  int32_t q0;
+  int32_t part0;
+  int32_t n_parts;
 };
 
 struct ExtendPlan {
   int32_t q_tile = 64;
   std::vector<ExtendConvDesc> convs;
   std::vector<ExtendTile> tiles;  // conversation-major (longest conversation first), heaviest tile first
+  // after split_extend:
+  int32_t piece = 0;    // key tiles per piece
+  int32_t n_parts = 0;  // pieces (per kv head)
+  std::vector<ExtendMerge> merges;
 };
 
 ExtendPlan plan_extend(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
                        const std::vector<int32_t>& q_lens, int32_t q_tile);
+
+// Cut the keys of a launch's tiles into pieces where the tiles alone would leave CUs idle; at most
+// max_records pieces over all kv heads. Changes nothing where the tiles fill the chip. Pieces are
+// counted from key tile 0 and all tiles of a launch are cut at multiples of one size, so a query's
+// result depends on that size and its position only.
+void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t max_records);
 
 // Append / unpack: one chunk = the part of one logical page a call writes.
 struct PageChunk {

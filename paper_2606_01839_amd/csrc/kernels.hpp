@@ -76,18 +76,15 @@ struct DecodeLaunch {
   int n_convs = 0, n_items = 0, split = 0;
 };
 
-// Decode: split kernel over plan items (partials), then the merge kernel (output).
+// Decode of n_layers consecutive layers from `layer` on in one launch: split kernel over plan items
+// (partials: n_layers x n_items x n_q_heads records), then the merge kernel (output). q and out:
+// [n_layers][n_convs][n_q_heads][head_dim].
 // direct_out != nullptr (only when every conversation is one item, n_items == n_convs): the split
 // writes the final output there and no merge follows.
-hipError_t launch_decode_split(const PoolGeom& g, int layer, const DecodeLaunch& w, const void* q,
+hipError_t launch_decode_split(const PoolGeom& g, int layer, int n_layers, const DecodeLaunch& w, const void* q,
                                float* partials, void* direct_out, hipStream_t stream);
-hipError_t launch_decode_merge(const PoolGeom& g, const DecodeLaunch& w, const float* partials, void* out,
-                               hipStream_t stream);
-// Merge of layer l (merge_partials -> merge_out) and split of layer split_layer (-> split_partials,
-// a different buffer) in one launch; the same conversations and plan for both.
-hipError_t launch_decode_merge_split(const PoolGeom& g, int split_layer, const DecodeLaunch& w, const void* q,
-                                     float* split_partials, const float* merge_partials,
-                                     void* merge_out, hipStream_t stream);
+hipError_t launch_decode_merge(const PoolGeom& g, int n_layers, const DecodeLaunch& w, const float* partials,
+                               void* out, hipStream_t stream);
 
 // Streaming-read probe: read `bytes` (a multiple of 16) of device memory once with non-temporal
 // 16-byte loads on 8 workgroups per CU; `sink` is 4 bytes of device memory (almost never written).
@@ -100,26 +97,40 @@ constexpr size_t kStaticScratchFloats = size_t(4) << 20;
 // with hipGetSymbolAddress and cached; allocates nothing).
 hipError_t static_decode_scratch(float** out);
 
+// Query rows (query tokens x query heads of the kv head) of an extend tile.
+constexpr int kExtendTileRows = 256;
+// Record of one piece of a cut extend tile and one kv head: o[256 rows][d] in accumulator order, then
+// (maximum, sum) for each of the 8 x 64 lanes.
+constexpr int extend_part_floats(int head_dim) { return kExtendTileRows * head_dim + 2 * 512; }
+
 // An extend plan as the kernels read it: meta = ExtendConvDesc[..], then (16-byte aligned, at
-// tiles_off) ExtendTile[n_tiles].
+// tiles_off) ExtendTile[n_tiles] and (at merges_off) ExtendMerge[n_merges].
 struct ExtendLaunch {
   Meta meta;
-  size_t tiles_off = 0;
-  int n_tiles = 0;
+  size_t tiles_off = 0, merges_off = 0;
+  int n_tiles = 0, n_merges = 0;
+  int piece = 0, n_parts = 0;
+  int64_t q_rows = 0;  // query rows of a layer
 };
 
-// One layer of a mixed step in one launch (head_dim 128 only): the extend tiles of the layer and
-// its decode split (partials; the merge follows as launch_decode_merge). Both plans uploaded.
+// One layer of a mixed step in one launch: the extend tiles of the layer and its decode split
+// (partials); launch_mixed_merge then combines the pieces of cut extend tiles and (out_dec !=
+// nullptr) the decode records in one launch. Both plans uploaded.
 hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q_ext,
-                              void* out_ext, const DecodeLaunch& w, const void* q_dec, float* partials,
-                              void* direct_out, hipStream_t stream);
+                              void* out_ext, float* parts, const DecodeLaunch& w, const void* q_dec,
+                              float* partials, void* direct_out, hipStream_t stream);
+hipError_t launch_mixed_merge(const PoolGeom& g, const ExtendLaunch& e, void* out_ext, float* parts,
+                              const DecodeLaunch& w, const float* partials, void* out_dec, hipStream_t stream);
 
-// Query tokens per extend/prefill work tile for this head size and GQA group (the host plan must
-// match).
-int extend_query_tile(int head_dim, int group);
+// Query tokens per extend/prefill work tile for this GQA group (the host plan must match).
+int extend_query_tile(int group);
 
-// Extend / prefill: one workgroup per (tile, kv head).
-hipError_t launch_extend(const PoolGeom& g, int layer, const ExtendLaunch& e, const void* q, void* out,
-                         hipStream_t stream);
+// Extend / prefill of n_layers consecutive layers from `layer` on: one workgroup per (tile or piece, kv
+// head, layer); then, where tiles are cut (n_merges > 0), the merge of their pieces. q and out:
+// [n_layers][q_rows][n_q_heads][head_dim]; parts: n_layers x n_parts x n_kv_heads records.
+hipError_t launch_extend(const PoolGeom& g, int layer, int n_layers, const ExtendLaunch& e, const void* q, void* out,
+                         float* parts, hipStream_t stream);
+hipError_t launch_extend_merge(const PoolGeom& g, int n_layers, const ExtendLaunch& e, void* out, float* parts,
+                               hipStream_t stream);
 
 }  // namespace cs

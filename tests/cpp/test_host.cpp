@@ -147,6 +147,61 @@ static void extend_plan() {
   CHECK(seen.size() == 5 && seen.count({0, 64}) && seen.count({1, 64}));
 }
 
+// Random launches: split_extend keeps the tiles' (conversation, query block) set, cuts a tile into
+// pieces that cover its key tiles once in whole pieces but the last, numbers the pieces of a tile one
+// after the other, stays within its records, and leaves a launch that fills the chip alone.
+static void extend_split_random() {
+  std::srand(777);
+  int cut = 0;
+  for (int trial = 0; trial < 400; ++trial) {
+    const int n = 1 + std::rand() % 6, hkv = 1 << (std::rand() % 4), q_tile = 32 << (std::rand() % 4);
+    std::vector<int32_t> slots(n), ql(n);
+    std::vector<int64_t> lens(n);
+    for (int i = 0; i < n; ++i) {
+      slots[i] = i;
+      ql[i] = 1 + std::rand() % (std::rand() % 2 ? 50 : 3000);
+      lens[i] = ql[i] + (std::rand() % 2 ? std::rand() % 60000 : 0);
+    }
+    const cs::ExtendPlan whole = cs::plan_extend(slots, lens, ql, q_tile);
+    cs::ExtendPlan p = whole;
+    cs::split_extend(p, hkv, 256, 512);
+    if (whole.tiles.size() > 2u * 256 / hkv) CHECK(p.merges.empty() && p.tiles.size() == whole.tiles.size());
+    if (p.merges.empty()) {
+      CHECK(p.n_parts == 0 && p.tiles.size() == whole.tiles.size());
+      continue;
+    }
+    ++cut;
+    CHECK(p.piece >= cs::kMinPiece && p.n_parts * hkv <= 512);
+    std::set<std::pair<int, int>> seen;
+    std::vector<int> part_seen(p.n_parts, 0);
+    for (const auto& t : p.tiles) {
+      if (t.part < 0) {
+        CHECK(t.k0 == 0 && seen.insert({t.conv, t.q0}).second);
+        continue;
+      }
+      CHECK(t.part < p.n_parts && !part_seen[t.part]);
+      part_seen[t.part] = 1;
+      CHECK(t.k0 % p.piece == 0);
+    }
+    int next = 0;
+    for (const auto& m : p.merges) {
+      CHECK(m.part0 == next && m.n_parts > 1 && seen.insert({m.conv, m.q0}).second);
+      next += m.n_parts;
+      const cs::ExtendConvDesc& c = p.convs[m.conv];
+      const int keys = (c.len - c.q_len + std::min(c.q_len, m.q0 + q_tile) + 63) / 64;
+      CHECK((m.n_parts - 1) * p.piece < keys && m.n_parts * p.piece >= keys);
+      for (int s = 0; s < m.n_parts; ++s) {
+        bool found = false;
+        for (const auto& t : p.tiles)
+          found = found || (t.part == m.part0 + s && t.conv == m.conv && t.q0 == m.q0 && t.k0 == s * p.piece);
+        CHECK(found);
+      }
+    }
+    CHECK(next == p.n_parts && seen.size() == whole.tiles.size());
+  }
+  CHECK(cut > 50);
+}
+
 static void append_plan() {
   std::vector<int32_t> pages0 = {7, 3};        // conversation with 20 tokens (2 pages) + 1 new
   std::vector<int32_t> pages1 = {5};           // empty conversation receiving 16 tokens
@@ -200,6 +255,7 @@ int main() {
   decode_plan();
   decode_plan_random();
   extend_plan();
+  extend_split_random();
   append_plan();
   std::puts("host metadata tests passed");
   return 0;
