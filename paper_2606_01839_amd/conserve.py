@@ -7,6 +7,7 @@ fallback. PyTorch only provides device memory and streams.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -90,12 +91,12 @@ def load_library(path: str = _LIB_PATH) -> ctypes.CDLL:
         "cs_conv_len": (I32, [P, I32, PI64]),
         "cs_conv_pages": (I32, [P, I32, PI32, I64, PI64]),
         "cs_kv_append": (I32, [P, I32, I32, VP, VP, VP]),
-        "cs_kv_append_batch": (I32, [P, I32, PI32, PI32, VP, VP, VP]),
-        "cs_attn_prefill_turn1": (I32, [P, I32, PI32, PI32, I32, VP, VP, VP]),
-        "cs_attn_extend": (I32, [P, I32, PI32, PI32, I32, VP, VP, VP]),
-        "cs_attn_decode_batch": (I32, [P, I32, PI32, I32, VP, VP, VP]),
-        "cs_attn_decode_batch_noalloc": (I32, [P, I32, PI32, I32, VP, VP, VP]),
-        "cs_mixed_step": (I32, [P, I32, PI32, PI32, I32, PI32, VP, VP, VP, VP, VP, VP, ctypes.c_uint32, VP]),
+        "cs_kv_append_batch": (I32, [P, I32, VP, VP, VP, VP, VP]),
+        "cs_attn_prefill_turn1": (I32, [P, I32, VP, VP, I32, VP, VP, VP]),
+        "cs_attn_extend": (I32, [P, I32, VP, VP, I32, VP, VP, VP]),
+        "cs_attn_decode_batch": (I32, [P, I32, VP, I32, VP, VP, VP]),
+        "cs_attn_decode_batch_noalloc": (I32, [P, I32, VP, I32, VP, VP, VP]),
+        "cs_mixed_step": (I32, [P, I32, VP, VP, I32, VP, VP, VP, VP, VP, VP, VP, ctypes.c_uint32, VP]),
         "cs_kv_pack_size": (I32, [P, I32, ctypes.POINTER(SZ)]),
         "cs_kv_pack": (I32, [P, I32, VP, SZ, VP]),
         "cs_kv_unpack": (I32, [P, VP, SZ, I64, PI32, VP]),
@@ -130,14 +131,21 @@ def _check(code: int) -> None:
 
 
 def _i32_array(xs):
-    a = np.ascontiguousarray(np.asarray(xs, dtype=np.int32).reshape(-1))
-    return a, a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+    """(int32 array of xs, its address); the array must outlive the address. A list of integers is
+    copied without numpy: 0.4 us instead of 1.7, of a decode call that takes 5 us in the library."""
+    try:
+        a = array.array("i", xs if type(xs) is list else np.asarray(xs, dtype=np.int32).reshape(-1).tolist())
+    except TypeError:           # not all integers: numpy's conversion
+        a = array.array("i", np.asarray(xs, dtype=np.int32).reshape(-1).tolist())
+    return a, a.buffer_info()[0]
 
 
 def _stream_handle(device: torch.device):
+    """Raw handle of the current stream (a Stream object around it costs 3.5 us a call)."""
     if device.type == "cuda":
-        return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
-    return ctypes.c_void_p(0)
+        index = device.index
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice() if index is None else index)
+    return None
 
 
 def _aligned_bytes(n: int, device: torch.device, align: int = 256) -> torch.Tensor:
@@ -244,8 +252,8 @@ class KVPool:
             raise ValueError(f"{name} must be on {self.device}, got {t.device}")
         if not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
-        if shape is not None and tuple(t.shape) != tuple(shape):
-            raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
+        if shape is not None and t.shape != shape:
+            raise ValueError(f"{name} must have shape {shape}, got {tuple(t.shape)}")
         return t.data_ptr()
 
     # -- KV append -----------------------------------------------------------------------------
@@ -259,25 +267,25 @@ class KVPool:
     def kv_append_batch(self, convs, n_new, k: torch.Tensor, v: torch.Tensor) -> None:
         ca, cp = _i32_array(convs)
         na, npp = _i32_array(n_new)
-        if ca.size != na.size:
+        if len(ca) != len(na):
             raise ValueError("convs and n_new differ in length")
-        shp = (self.n_layers, int(na.sum()), self.n_kv_heads, self.head_dim)
+        shp = (self.n_layers, sum(na), self.n_kv_heads, self.head_dim)
         kp, vp = self._dev(k, "k", shp), self._dev(v, "v", shp)
-        _check(self.lib.cs_kv_append_batch(self._handle, ca.size, cp, npp, kp, vp,
+        _check(self.lib.cs_kv_append_batch(self._handle, len(ca), cp, npp, kp, vp,
                                            _stream_handle(self.device)))
 
     # -- attention -----------------------------------------------------------------------------
     def _attend(self, fn, convs, q_lens, layer, q, out):
         ca, cp = _i32_array(convs)
         qa, qp = _i32_array(q_lens)
-        if ca.size != qa.size:
+        if len(ca) != len(qa):
             raise ValueError("convs and q_lens differ in length")
-        shp = (int(qa.sum()), self.n_q_heads, self.head_dim)
+        shp = (sum(qa), self.n_q_heads, self.head_dim)
         qptr = self._dev(q, "q", shp)
         if out is None:
             out = torch.empty(shp, dtype=torch.bfloat16, device=self.device)
         optr = self._dev(out, "out", shp)
-        _check(fn(self._handle, ca.size, cp, qp, layer, qptr, optr, _stream_handle(self.device)))
+        _check(fn(self._handle, len(ca), cp, qp, layer, qptr, optr, _stream_handle(self.device)))
         return out
 
     def attn_prefill_turn1(self, convs, q_lens, layer, q, out=None) -> torch.Tensor:
@@ -295,12 +303,12 @@ class KVPool:
 
     def _decode(self, fn, convs, layer, q, out):
         ca, cp = _i32_array(convs)
-        shp = (ca.size, self.n_q_heads, self.head_dim)
+        shp = (len(ca), self.n_q_heads, self.head_dim)
         qptr = self._dev(q, "q", shp)
         if out is None:
             out = torch.empty(shp, dtype=torch.bfloat16, device=self.device)
         optr = self._dev(out, "out", shp)
-        _check(fn(self._handle, ca.size, cp, layer, qptr, optr, _stream_handle(self.device)))
+        _check(fn(self._handle, len(ca), cp, layer, qptr, optr, _stream_handle(self.device)))
         return out
 
     def mixed_step(self, ext_convs, ext_lens, dec_convs, k, v, q_ext=None, q_dec=None,
@@ -312,9 +320,9 @@ class KVPool:
         ea, ep = _i32_array(ext_convs)
         la, lp = _i32_array(ext_lens)
         da, dp = _i32_array(dec_convs)
-        if ea.size != la.size:
+        if len(ea) != len(la):
             raise ValueError("ext_convs and ext_lens differ in length")
-        ne, nd, L = int(la.sum()), da.size, self.n_layers
+        ne, nd, L = sum(la), len(da), self.n_layers
         kv_shape = (L, ne + nd, self.n_kv_heads, self.head_dim)
         kp, vp = self._dev(k, "k", kv_shape), self._dev(v, "v", kv_shape)
         eshape = (L, ne, self.n_q_heads, self.head_dim)
@@ -331,7 +339,7 @@ class KVPool:
                 out_dec = torch.empty(dshape, dtype=torch.bfloat16, device=self.device)
             od = self._dev(out_dec, "out_dec", dshape)
         flags = CS_MIXED_LAYER_ORDERED if layer_ordered else 0
-        _check(self.lib.cs_mixed_step(self._handle, ea.size, ep, lp, nd, dp, kp, vp, qe, oe, qd, od,
+        _check(self.lib.cs_mixed_step(self._handle, len(ea), ep, lp, nd, dp, kp, vp, qe, oe, qd, od,
                                       flags, _stream_handle(self.device)))
         return out_ext, out_dec
 

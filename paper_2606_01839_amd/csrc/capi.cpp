@@ -9,7 +9,6 @@
 #include <cstring>
 #include <new>
 #include <string>
-#include <unordered_set>
 #include <vector>
 
 #include "host/host_state.hpp"
@@ -119,6 +118,9 @@ struct cs_pool {
   hipEvent_t span_start = nullptr;
   hipStream_t span_stream = nullptr;
   int span_kind = 0, span_launches = 0;
+  // check_convs: the batch that last named each conversation slot
+  std::vector<uint32_t> seen;
+  uint32_t batch = 0;
   std::vector<hipEvent_t> ev_free;
   std::vector<ProfEvent> prof_events;
 
@@ -356,16 +358,25 @@ cs::Meta meta_part(const void* dev, size_t off, size_t bytes) {
   return m;
 }
 
-cs_status check_convs(const cs_pool* p, int32_t n, const cs_conv* convs, std::vector<const cs::Conv*>& out) {
+cs_status check_convs(cs_pool* p, int32_t n, const cs_conv* convs, std::vector<const cs::Conv*>& out) {
   if (n < 0) return fail(CS_EINVAL, "negative batch size");
   if (n > 0 && !convs) return fail(CS_EINVAL, "null conversation array");
   out.clear();
-  std::unordered_set<int32_t> seen;
+  out.reserve(static_cast<size_t>(n));
+  // Slots of this batch are stamped with its number (one slot has one valid handle at a time); the
+  // stamps start over when the counter wraps.
+  if (p->seen.empty()) p->seen.assign(static_cast<size_t>(p->desc.max_convs), 0);
+  if (++p->batch == 0) {
+    std::fill(p->seen.begin(), p->seen.end(), 0u);
+    p->batch = 1;
+  }
   for (int32_t i = 0; i < n; ++i) {
     const cs::Conv* c = p->convs.find(convs[i]);
     if (!c) return fail(CS_ENOENT, "unknown conversation handle " + std::to_string(convs[i]));
-    if (!seen.insert(convs[i]).second)
+    uint32_t& mark = p->seen[static_cast<size_t>(cs::ConvTable::slot_of(convs[i]))];
+    if (mark == p->batch)
       return fail(CS_EINVAL, "conversation " + std::to_string(convs[i]) + " appears twice in a batch");
+    mark = p->batch;
     out.push_back(c);
   }
   return CS_OK;
