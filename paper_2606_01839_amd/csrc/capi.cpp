@@ -34,12 +34,18 @@ constexpr int64_t kDecodeTargetItems = 4096;
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 constexpr int kMaxLayersPerLaunch = 32768;  // a grid dimension
-// Records of cut extend tiles one launch may write: two per CU (68 MB of workspace at head dim 128).
+// Records of cut extend tiles one layer may write: two per CU.
 constexpr int kExtendRecords = 2 * cs::kCus;
+// Records the workspace holds (68 MB at head dim 128; 203 MB in a multi-layer pool, whose overlapped
+// steps put as many layers into one launch as have room: 28 layers of a 4-conversation step in one
+// launch instead of three 395 -> 374 us, 32 of an 8-conversation one 1614 -> 1527 us).
+int extend_records(const cs_pool_desc& d) { return (d.n_layers > 1 ? 3 : 1) * kExtendRecords; }
 
 struct WsLayout {
   size_t page_table, partials, ext_parts, ring, total;
-  size_t partial_floats;  // decode records: at least one layer of any batch, two in a multi-layer pool
+  // decode records: one layer of any batch, two in a multi-layer pool, and every layer of a batch whose
+  // items fit the CUs in one round (17 MB at 32 layers, 32 query heads, head dim 128)
+  size_t partial_floats;
 };
 
 int64_t max_decode_items(const cs_pool_desc& d) {
@@ -52,12 +58,13 @@ WsLayout ws_layout(const cs_pool_desc& d) {
   w.page_table = 0;
   size_t pt_bytes = static_cast<size_t>(d.max_convs) * static_cast<size_t>(d.max_pages_per_conv) * 4;
   w.partials = align_up(pt_bytes, kAlign);
-  w.partial_floats = static_cast<size_t>(max_decode_items(d)) * d.n_q_heads * cs::partial_floats(d.head_dim) *
-                     (d.n_layers > 1 ? 2 : 1);
+  const int64_t one_round = std::max(1, cs::kCus / d.n_kv_heads) * static_cast<int64_t>(d.n_layers);
+  w.partial_floats = static_cast<size_t>(std::max(max_decode_items(d) * (d.n_layers > 1 ? 2 : 1), one_round)) *
+                     d.n_q_heads * cs::partial_floats(d.head_dim);
   w.ext_parts = align_up(w.partials + w.partial_floats * 4, kAlign);
   // a pool whose longest conversation is too short to be cut needs no records
   const int64_t longest = std::min<int64_t>(d.max_pages_per_conv, d.n_pages) * cs::kPage;
-  const size_t records = longest > cs::kExtendKeyTile * cs::kMinPiece ? kExtendRecords : 0;
+  const size_t records = longest > cs::kExtendKeyTile * cs::kMinPiece ? extend_records(d) : 0;
   w.ring = align_up(w.ext_parts + records * cs::extend_part_floats(d.head_dim) * 4, kAlign);
   w.total = w.ring + kRingBytes;
   return w;
@@ -445,7 +452,7 @@ cs_status launch_extend_layers(cs_pool* p, const ExtendWork& w, int layer, int n
   const size_t row_bytes = static_cast<size_t>(g.n_q_heads) * g.head_dim * 2;
   for (const auto& e : w.parts) {
     const int per = std::min(kMaxLayersPerLaunch,
-                             e.n_parts == 0 ? n_layers : std::max(1, kExtendRecords / (e.n_parts * g.n_kv_heads)));
+                             e.n_parts == 0 ? n_layers : std::max(1, extend_records(p->desc) / (e.n_parts * g.n_kv_heads)));
     for (int l = 0; l < n_layers; l += per) {
       const int nl = std::min(per, n_layers - l);
       const char* ql = static_cast<const char*>(q) + l * e.q_rows * row_bytes;
@@ -470,7 +477,7 @@ struct DecodeWork {
 
 cs::DecodePlan plan_decode_batch(const cs_pool* p, const std::vector<int32_t>& slots,
                                  const std::vector<int64_t>& lens) {
-  return cs::plan_decode(slots, lens, p->desc.n_kv_heads, kDecodeTargetItems);
+  return cs::plan_decode_filling(slots, lens, p->desc.n_kv_heads, kDecodeTargetItems, cs::kCus);
 }
 
 // Descriptors and launch order of a decode plan, as laid out back to back.

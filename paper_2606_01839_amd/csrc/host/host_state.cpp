@@ -84,17 +84,10 @@ void ConvTable::destroy(int32_t handle, PagePool& pool) {
   free_slots_.push_back(s);
 }
 
-DecodePlan plan_decode(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
-                       int32_t n_kv_heads, int64_t target_items) {
-  static const int32_t kCandidates[] = {1024, 512, 256, 128};
+// The items and launch order of a plan with splits of `split` keys.
+static DecodePlan decode_plan_of(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens, int32_t split) {
   DecodePlan plan;
-  for (int32_t split : kCandidates) {
-    int64_t items = 0;
-    for (int64_t L : lens) items += (L + split - 1) / split;
-    plan.split_tokens = split;
-    if (items * n_kv_heads >= target_items) break;
-  }
-  const int32_t split = plan.split_tokens;
+  plan.split_tokens = split;
   const int64_t item_keys = static_cast<int64_t>(kDecodeSubSplits) * split;
   int32_t start = 0;
   plan.convs.reserve(lens.size());
@@ -112,6 +105,34 @@ DecodePlan plan_decode(const std::vector<int32_t>& slots, const std::vector<int6
   std::iota(plan.order.begin(), plan.order.end(), 0);
   std::stable_sort(plan.order.begin(), plan.order.end(),
                    [&](int32_t x, int32_t y) { return keys[x] > keys[y]; });
+  return plan;
+}
+
+DecodePlan plan_decode(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
+                       int32_t n_kv_heads, int64_t target_items) {
+  static const int32_t kCandidates[] = {1024, 512, 256, 128};
+  int32_t split = 0;
+  for (int32_t c : kCandidates) {
+    int64_t items = 0;
+    for (int64_t L : lens) items += (L + c - 1) / c;
+    split = c;
+    if (items * n_kv_heads >= target_items) break;
+  }
+  return decode_plan_of(slots, lens, split);
+}
+
+DecodePlan plan_decode_filling(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
+                               int32_t n_kv_heads, int64_t target_items, int32_t n_cus) {
+  DecodePlan plan = plan_decode(slots, lens, n_kv_heads, target_items);
+  if (static_cast<int64_t>(plan.n_items) * n_kv_heads >= n_cus) return plan;
+  for (const DecodeConvDesc& c : plan.convs)
+    if (c.n_splits < 2) return plan;
+  for (int32_t split = 32; split < plan.split_tokens; split += 32) {
+    int64_t items = 0;
+    const int64_t item_keys = static_cast<int64_t>(kDecodeSubSplits) * split;
+    for (int64_t L : lens) items += (L + item_keys - 1) / item_keys;
+    if (items * n_kv_heads <= n_cus) return decode_plan_of(slots, lens, split);
+  }
   return plan;
 }
 

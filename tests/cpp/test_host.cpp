@@ -133,6 +133,45 @@ static void decode_plan_random() {
   }
 }
 
+// plan_decode_filling: the plan of plan_decode unless its items leave CUs without one and every
+// conversation has several; then the smallest splits whose items fit one round.
+static void decode_plan_filling() {
+  std::srand(4242);
+  int refined = 0;
+  for (int trial = 0; trial < 400; ++trial) {
+    const int n = 1 + std::rand() % 6, hkv = 1 << (std::rand() % 4);
+    std::vector<int32_t> slots(n);
+    std::vector<int64_t> lens(n);
+    for (int i = 0; i < n; ++i) {
+      slots[i] = i;
+      lens[i] = 1 + std::rand() % (std::rand() % 8 ? 9000 : 900);
+    }
+    const cs::DecodePlan base = cs::plan_decode(slots, lens, hkv, 4096);
+    const cs::DecodePlan p = cs::plan_decode_filling(slots, lens, hkv, 4096, 256);
+    bool multi = true;
+    for (const auto& c : base.convs) multi = multi && c.n_splits > 1;
+    int64_t keys = 0, total = 0;
+    for (int i = 0; i < n; ++i) {
+      CHECK(p.convs[i].len == lens[i] && p.convs[i].item_start == total);
+      CHECK(static_cast<int64_t>(p.convs[i].n_splits - 1) * 8 * p.split_tokens < lens[i]);
+      CHECK(static_cast<int64_t>(p.convs[i].n_splits) * 8 * p.split_tokens >= lens[i]);
+      total += p.convs[i].n_splits;
+      keys += lens[i];
+    }
+    CHECK(p.n_items == total && p.order.size() == static_cast<size_t>(total) && p.split_tokens % 32 == 0);
+    if (p.split_tokens == base.split_tokens) continue;
+    ++refined;
+    CHECK(multi && base.n_items * hkv < 256 && p.n_items * hkv <= 256 && p.split_tokens < base.split_tokens);
+    CHECK(!p.single_item && p.n_items <= keys / 128 + n);   // the records' room
+    if (p.split_tokens > 32) {
+      int64_t finer = 0;
+      for (int64_t L : lens) finer += (L + 8 * (p.split_tokens - 32) - 1) / (8 * (p.split_tokens - 32));
+      CHECK(finer * hkv > 256);
+    }
+  }
+  CHECK(refined > 50);
+}
+
 static void extend_plan() {
   std::vector<int32_t> slots = {0, 1};
   std::vector<int64_t> lens = {100, 300};
@@ -254,6 +293,7 @@ int main() {
   conv_table();
   decode_plan();
   decode_plan_random();
+  decode_plan_filling();
   extend_plan();
   extend_split_random();
   append_plan();

@@ -78,3 +78,23 @@ def test_mixed_step_with_cut_tiles_equals_separate_calls(hq, hkv, d, ordered):
             assert torch.equal(od[l], b.attn_decode_batch(hb[1:], l, qd[l])), l
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 1, 64), (8, 8, 128)])
+@pytest.mark.parametrize("lens", [[1025], [2047], [6000], [24571], [1100, 4096, 2500], [1500, 900]], ids=str)
+def test_decode_filling_splits_match_oracle(hq, hkv, d, lens):
+    """Decode batches small enough to get splits of 32, 64 or 96 keys (and one that keeps its plan: it
+    holds a conversation of one item), with and without the allocation-free entry point."""
+    from paper_2606_01839_amd import KVPool
+    pool = KVPool(1, hq, hkv, d, n_pages=sum((n + 15) // 16 for n in lens) + 8, max_convs=4, max_pages_per_conv=2048,
+                  placement_seed=2, device="cuda")
+    kv = [kv_tokens(SEED, i, 1, 0, n, hkv, d) for i, n in enumerate(lens)]
+    convs = [pool.conv_create() for _ in lens]
+    for c, (k, v) in zip(convs, kv):
+        pool.kv_append(c, k.cuda(), v.cuda())
+    q = torch.cat([q_tokens(SEED, i, 0, n - 1, 1, hq, d) for i, n in enumerate(lens)])
+    out = pool.attn_decode_batch(convs, 0, q.cuda())
+    assert torch.equal(out, pool.attn_decode_batch_noalloc(convs, 0, q.cuda(), torch.empty_like(out)))
+    for i in range(len(lens)):
+        assert_close(out[i:i + 1], attend_last(f64(q[i:i + 1]), f64(kv[i][0][0]), f64(kv[i][1][0])), f"conv {i}")
+    pool.close()
