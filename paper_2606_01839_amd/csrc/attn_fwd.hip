@@ -21,7 +21,9 @@
 // A workgroup sweeps its tile's keys one after another, so a launch with fewer tiles than the chip
 // has CUs takes as long as its longest tile. The host then cuts the tiles' keys into pieces
 // (split_extend in host_state.cpp): each piece is a workgroup that writes its unnormalised output, row
-// maximum and row sum, and extend_merge_kernel combines the pieces of a tile in their order.
+// maximum and row sum, and extend_merge_kernel combines the pieces of a tile in their order. Where other
+// work fills the CUs (a mixed step's decode, many layers in one launch) one workgroup takes a tile's
+// pieces one after the other instead and combines them itself, with the same result bit for bit.
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -105,7 +107,9 @@ __device__ __forceinline__ void dma_wait_barrier() {
 // PRE: the K operands of the next tile and the V operands of this one are read from LDS ahead of the
 // matrix instructions that use them (two waves per SIMD have little else to cover the LDS latency).
 // Without it a head_dim 64 wave needs 121 registers and two workgroups fit a CU.
-template <int D, int G, bool PRE>
+// CHAIN: tiles may hold pieces to take one after the other (a form of its own, since the code around
+// the loop costs launches without such tiles 1.5%).
+template <int D, int G, bool PRE, bool CHAIN>
 __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int block, const int dl) {
   constexpr int NW = 8;                   // waves: G query heads x (8 / G) blocks of 32 queries
   constexpr int BM = 32 * (NW / G);       // queries per workgroup
@@ -133,7 +137,9 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
   const int q_hi = min(cd.q_len, tile.q0 + BM);
   const int pos_min = prefix + tile.q0, pos_max = prefix + q_hi - 1;
   // key tiles [kt0, n_kt): all that the tile sees, or one piece of them
-  const int kt0 = tile.k0;
+  const bool chained = CHAIN && tile.k0 < 0;                  // a cut tile's pieces one after the other
+  const int kt0 = chained ? 0 : tile.k0;
+  int part = chained ? -1 - tile.k0 : tile.part;     // record of the piece
   const int n_kt = tile.part < 0 ? pos_max / kBN + 1 : min(pos_max / kBN + 1, kt0 + a.piece);
   const int n_pg = (cd.len + kPageTokens - 1) / kPageTokens;
   const int32_t* pt = a.page_table + static_cast<size_t>(cd.slot) * a.max_pages;
@@ -345,29 +351,88 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
     // barrier every wave's have.
     dma_wait_barrier<2 * BPW>();
   };
-  for (int j = kt0; j < n_kt; j += 4) {
-    tile_step(j, 0);
-    if (j + 1 < n_kt) tile_step(j + 1, 1);
-    if (j + 2 < n_kt) tile_step(j + 2, 2);
-    if (j + 3 < n_kt) tile_step(j + 3, 3);
-  }
-  // no copy may land after the workgroup ends, nor in what follows
-  dma_wait_barrier<0>();
-
-  const float l_tot = halves_sum(l_run);
-  if (tile.part >= 0) {
-    // One piece: the accumulators as they lie in the registers (every store 1 KiB of consecutive
-    // bytes per wave), then (maximum, sum) of each lane's row.
-    float* rec = a.parts + dl * a.part_stride +
-                 (static_cast<size_t>(tile.part) * a.n_kv_heads + g) * extend_part_floats(D);
+  // One piece's record: the accumulators as they lie in the registers (every store 1 KiB of consecutive
+  // bytes per wave), then (maximum, sum) of each lane's row.
+  auto record = [&](int pt_) {
+    return a.parts + dl * a.part_stride + (static_cast<size_t>(pt_) * a.n_kv_heads + g) * extend_part_floats(D);
+  };
+  auto write_record = [&]() {
+    float* rec = record(part);
     f32x4* ow = reinterpret_cast<f32x4*>(rec) + wave * (4 * DT * 64) + lane;
 #pragma unroll
     for (int t = 0; t < DT; ++t)
 #pragma unroll
       for (int e4 = 0; e4 < 4; ++e4)
         ow[(4 * t + e4) * 64] = f32x4{o[t][4 * e4], o[t][4 * e4 + 1], o[t][4 * e4 + 2], o[t][4 * e4 + 3]};
-    reinterpret_cast<f32x2*>(rec + kExtendTileRows * D)[wave * 64 + lane] = f32x2{m_s, l_tot};
+    reinterpret_cast<f32x2*>(rec + kExtendTileRows * D)[wave * 64 + lane] = f32x2{m_s, halves_sum(l_run)};
+  };
+  float m_all = -FLT_MAX;   // over the pieces already recorded
+  int kb = kt0, ke = chained ? min(n_kt, a.piece) : n_kt;   // a.piece is a multiple of the ring's four buffers
+  for (;;) {
+    for (int j = kb; j < ke; j += 4) {
+      tile_step(j, 0);
+      if (j + 1 < ke) tile_step(j + 1, 1);
+      if (j + 2 < ke) tile_step(j + 2, 2);
+      if (j + 3 < ke) tile_step(j + 3, 3);
+    }
+    if (!CHAIN || ke == n_kt) break;
+    // The stores stay in flight: the loop's waits count them too and so only wait for more (loads return
+    // in order among themselves: with at most N operations left, the loads left are the newest N).
+    write_record();
+    m_all = fmaxf(m_all, m_s);
+    ++part;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[t][e] = 0.f;
+    m_s = -FLT_MAX;
+    l_run = 0.f;
+    kb = ke;
+    ke = min(n_kt, ke + a.piece);
+  }
+  // no copy may land after the workgroup ends, nor in what follows
+  dma_wait_barrier<0>();
+
+  if (tile.part >= 0) {
+    write_record();
     return;
+  }
+  float l_tot = halves_sum(l_run);
+  if (chained) {
+    // Combine with the records of the pieces before, as extend_merge_body does (this wave wrote them
+    // and has waited for the stores).
+    const int part0 = -1 - tile.k0;
+    const size_t stride = static_cast<size_t>(a.n_kv_heads) * extend_part_floats(D);
+    const float* ml = record(part0) + kExtendTileRows * D + (wave * 64 + lane) * 2;
+    const float* src = record(part0) + (wave * 4 * DT * 64 + lane) * 4;
+    const float M = fmaxf(m_all, m_s);
+    float l = 0.f;
+    f32x16 acc[DT];
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+    for (int i = 0; i < part - part0; ++i) {
+      const f32x2 x = *reinterpret_cast<const f32x2*>(ml + i * stride);
+      f32x4 v[DT][4];
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+          v[t][e4] = *reinterpret_cast<const f32x4*>(src + i * stride + (4 * t + e4) * 256);
+      const float wt = fast_exp2(x.x - M);
+      l = __builtin_fmaf(wt, x.y, l);
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] = __builtin_fmaf(wt, v[t][e / 4][e % 4], acc[t][e]);
+    }
+    const float w_last = fast_exp2(m_s - M);
+    l_tot = __builtin_fmaf(w_last, l_tot, l);
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[t][e] = __builtin_fmaf(w_last, o[t][e], acc[t][e]);
   }
   // Through the wave's own part of LDS (rows padded by 16 bytes), so that a store writes whole rows (64
   // lanes: RPB rows of 2 D bytes) instead of 8 bytes in each of 32 rows.
@@ -443,10 +508,10 @@ __device__ __forceinline__ void extend_merge_body(const ExtendArgs& a, const int
 }
 
 // blockIdx.y: layer (consecutive layers of one launch share the plan)
-template <int D, int G, bool PRE>
+template <int D, int G, bool PRE, bool CHAIN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PRE ? 2 : 4)))
 void attn_fwd_kernel(LaunchMeta, ExtendArgs a) {
-  attn_fwd_block<D, G, PRE>(a, blockIdx.x, blockIdx.y);
+  attn_fwd_block<D, G, PRE, CHAIN>(a, blockIdx.x, blockIdx.y);
 }
 
 template <int D, int G>
@@ -461,7 +526,7 @@ __global__ __launch_bounds__(256) void extend_merge_kernel(LaunchMeta, ExtendArg
 // Units of n_kv_heads workgroups are taken in an order that spreads the extend units evenly over the
 // first n_mix units, so that at any time some CUs use the matrix cores while others read HBM; n_mix =
 // their number puts them all in front (tiles longer than everything else).
-template <int D, int G>
+template <int D, int G, bool CHAIN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 void mixed_layer_kernel(ExtendArgs ea, int n_ext, int n_mix, DecodeArgs da) {
   static_assert(kDecodeItemThreads == 512, "a decode work item fills one attention workgroup");
@@ -470,7 +535,7 @@ void mixed_layer_kernel(ExtendArgs ea, int n_ext, int n_mix, DecodeArgs da) {
   const int before = unit < n_mix ? static_cast<int>(static_cast<int64_t>(unit) * n_ext / n_mix) : n_ext;
   const int after = unit < n_mix ? static_cast<int>(static_cast<int64_t>(unit + 1) * n_ext / n_mix) : n_ext;
   if (after > before) {
-    attn_fwd_block<D, G, true>(ea, before * ea.n_kv_heads + head, 0);
+    attn_fwd_block<D, G, true, CHAIN>(ea, before * ea.n_kv_heads + head, 0);
     return;
   }
   split_body<D>(da, (unit - before) * ea.n_kv_heads + head, 0, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), xch);
@@ -543,15 +608,16 @@ hipError_t launch_extend(const PoolGeom& g, int layer, int n_layers, const Exten
   // its operands ahead is the faster form: 4500 (568) 98 against 106 us, 2500 (320) 41 against 45. A
   // head_dim 128 workgroup fills its CU's LDS.
   const bool two_per_cu = static_cast<int64_t>(grid.x) * grid.y > 5 * kCus / 2;
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, 512, 0, stream>>>(m, a);
+    return hipGetLastError();
+  };
   return by_shape(g, [&](auto d, auto grp) {
     if constexpr (d() == 64) {
-      if (two_per_cu) {
-        attn_fwd_kernel<d(), grp(), false><<<grid, 512, 0, stream>>>(m, a);
-        return hipGetLastError();
-      }
+      if (two_per_cu)
+        return e.chained ? launch(attn_fwd_kernel<d(), grp(), false, true>) : launch(attn_fwd_kernel<d(), grp(), false, false>);
     }
-    attn_fwd_kernel<d(), grp(), true><<<grid, 512, 0, stream>>>(m, a);
-    return hipGetLastError();
+    return e.chained ? launch(attn_fwd_kernel<d(), grp(), true, true>) : launch(attn_fwd_kernel<d(), grp(), true, false>);
   });
 }
 
@@ -578,14 +644,15 @@ hipError_t launch_mixed_layer(const PoolGeom& g, int layer, const ExtendLaunch& 
   const ExtendArgs ea = make_extend_args(g, layer, e, q_ext, out_ext, parts);
   DecodeArgs da = make_decode_args(g, layer, w, q_dec, direct_out, partials);
   da.direct = direct_out != nullptr;
-  // Cut tiles (all pieces short) are spread over the first 60% of the decode items; whole tiles go in
-  // front of them. Layers of 16 conversations (2k-12k tokens, a 513-token chunk): 4.20-4.33 ms per 32-layer
+  // Pieces of cut tiles (all short) are spread over the first 60% of the decode items; whole and chained
+  // tiles go in front of them. Layers of 16 conversations (2k-12k tokens, a 513-token chunk): 4.20-4.33 ms per 32-layer
   // step with the pieces in front, 4.06 spread over 40%, 4.05 over 70%, 4.72 over all; 16 x 4k tokens and
   // a 300-token chunk 3.19, 2.88, 2.70, 2.92.
-  const int n_mix = e.n_tiles + (e.n_parts > 0 ? w.n_items * 6 / 10 : 0);
+  const int n_mix = e.n_tiles + (e.n_merges > 0 ? w.n_items * 6 / 10 : 0);
   const int blocks = (e.n_tiles + w.n_items) * g.n_kv_heads;
   return by_shape(g, [&](auto d, auto grp) {
-    mixed_layer_kernel<d(), grp()><<<blocks, 512, 0, stream>>>(ea, e.n_tiles, n_mix, da);
+    if (e.chained) mixed_layer_kernel<d(), grp(), true><<<blocks, 512, 0, stream>>>(ea, e.n_tiles, n_mix, da);
+    else mixed_layer_kernel<d(), grp(), false><<<blocks, 512, 0, stream>>>(ea, e.n_tiles, n_mix, da);
     return hipGetLastError();
   });
 }

@@ -214,8 +214,9 @@ void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t m
   for (int rounds = 1; rounds <= 4; ++rounds) {
     // the smallest size whose pieces fit in this many rounds of the CUs, and their records
     int32_t c = std::max<int32_t>(kMinPiece, static_cast<int32_t>(total / (static_cast<int64_t>(rounds) * slots)));
+    c = (c + kPieceStep - 1) / kPieceStep * kPieceStep;
     int pieces = 0, parts = 0;
-    for (;; c += std::max(1, c / 16)) {
+    for (;; c += std::max(1, c / 16 / kPieceStep) * kPieceStep) {
       pieces = parts = 0;
       for (int32_t k : keys) {
         const int np = (k + c - 1) / c;
@@ -257,6 +258,52 @@ void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t m
   std::stable_sort(work.begin(), work.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
   plan.tiles.clear();
   for (auto& w : work) plan.tiles.push_back(w.second);
+}
+
+void chain_extend(ExtendPlan& plan) {
+  std::vector<std::pair<int32_t, ExtendTile>> work;
+  auto keys_of = [&](const ExtendTile& t) {
+    const ExtendConvDesc& c = plan.convs[static_cast<size_t>(t.conv)];
+    return c.len - c.q_len + std::min(c.q_len, t.q0 + plan.q_tile);
+  };
+  for (const ExtendTile& t : plan.tiles)
+    if (t.part < 0) work.push_back({keys_of(t), t});
+  for (const ExtendMerge& m : plan.merges) {
+    const ExtendTile t{m.conv, m.q0, -1 - m.part0, -1};
+    work.push_back({keys_of(t), t});
+  }
+  std::stable_sort(work.begin(), work.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  plan.tiles.clear();
+  for (auto& w : work) plan.tiles.push_back(w.second);
+  plan.merges.clear();
+}
+
+bool chain_pays(const ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t n_layers, float other_steps) {
+  if (plan.merges.empty()) return false;
+  const float slots = static_cast<float>(std::max(1, n_cus / n_kv_heads));
+  float keys = 0.f, longest = 0.f;
+  int whole = static_cast<int>(plan.merges.size());
+  auto add = [&](int32_t conv, int32_t q0, bool cut) {
+    const ExtendConvDesc& c = plan.convs[static_cast<size_t>(conv)];
+    const int32_t seen = c.len - c.q_len + std::min(c.q_len, q0 + plan.q_tile);
+    const float k = static_cast<float>((seen + kExtendKeyTile - 1) / kExtendKeyTile);
+    keys += k;
+    // a chained tile writes and reads back a record (about two steps) for every piece but its last
+    longest = std::max(longest, k + (cut ? 2.f * k / static_cast<float>(plan.piece) : 0.f));
+  };
+  for (const ExtendMerge& m : plan.merges) add(m.conv, m.q0, true);
+  for (const ExtendTile& t : plan.tiles)
+    if (t.part < 0) {
+      add(t.conv, t.q0, false);
+      ++whole;
+    }
+  const float nl = static_cast<float>(n_layers);
+  const float work = nl * (keys + other_steps) / slots, start = nl * kStartSteps / slots;
+  const float chained = std::max(longest + kStartSteps, work + start * static_cast<float>(whole) +
+                                                             nl * 2.f * static_cast<float>(plan.n_parts) / slots);
+  const float apart = work + start * static_cast<float>(plan.tiles.size()) +
+                      kMergeSteps / 2 + nl * kRecordSteps * static_cast<float>(plan.n_parts * n_kv_heads);
+  return chained <= apart;
 }
 
 std::vector<PageChunk> plan_append(const std::vector<int32_t>& slots,

@@ -135,11 +135,13 @@ constexpr int kExtendKeyTile = 64;  // keys per step of the attention kernel
 // 3000 tokens takes 22.1 us with 6, 24.1 with 8 (65 uncut), but a step of 8 conversations over 32 layers
 // 2134 / 2062 us and one of 4 over 28 layers in one launch 391 / 366, where other work fills the CUs.
 constexpr int kMinPiece = 8;
+constexpr int kPieceStep = 4;       // a piece is a multiple of the buffers of the kernel's LDS ring
 
 struct ExtendTile {
   int32_t conv;       // index into the batch
   int32_t q0;         // first query index (0-based within the conversation's q_len)
-  int32_t k0 = 0;     // first key tile
+  int32_t k0 = 0;     // first key tile; -1 - part0 < 0: a cut tile whose pieces part0, part0 + 1, ... one
+                      // workgroup takes one after the other (part = -1)
   int32_t part = -1;  // -1: every key tile the queries see; else piece `part` of the launch: key
                       // tiles [k0, k0 + ExtendPlan::piece) of them
 };
@@ -170,6 +172,15 @@ ExtendPlan plan_extend(const std::vector<int32_t>& slots, const std::vector<int6
 // counted from key tile 0 and all tiles of a launch are cut at multiples of one size, so a query's
 // result depends on that size and its position only.
 void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t max_records);
+
+// The same cuts, but one workgroup for each tile: it takes the tile's pieces one after the other and
+// combines them itself (bit for bit what separate pieces and their merge give, without their start-up,
+// their merge launch and most of their records' way to memory).
+void chain_extend(ExtendPlan& plan);
+
+// Whether chain_extend makes the launch shorter where other work waits for the CUs too: other_steps of
+// it for each layer and kv head (in CU-steps of a key tile), n_layers layers in the launch.
+bool chain_pays(const ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t n_layers, float other_steps);
 
 // Append / unpack: one chunk = the part of one logical page a call writes.
 struct PageChunk {

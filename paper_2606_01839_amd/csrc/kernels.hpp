@@ -110,6 +110,7 @@ struct ExtendLaunch {
   size_t tiles_off = 0, merges_off = 0;
   int n_tiles = 0, n_merges = 0;
   int piece = 0, n_parts = 0;
+  bool chained = false;  // some tiles hold their pieces (ExtendTile::k0 < 0)
   int64_t q_rows = 0;  // query rows of a layer
 };
 

@@ -236,7 +236,21 @@ static void extend_split_random() {
         CHECK(found);
       }
     }
-    CHECK(next == p.n_parts && seen.size() == whole.tiles.size());
+    CHECK(next == p.n_parts && seen.size() == whole.tiles.size() && p.piece % cs::kPieceStep == 0);
+    // chained: one workgroup per tile, the cut ones naming their first record
+    cs::ExtendPlan ch = p;
+    cs::chain_extend(ch);
+    CHECK(ch.merges.empty() && ch.n_parts == p.n_parts && ch.piece == p.piece && ch.tiles.size() == whole.tiles.size());
+    std::set<std::pair<int, int>> tiles;
+    for (const auto& t : ch.tiles) {
+      CHECK(t.part == -1 && tiles.insert({t.conv, t.q0}).second);
+      const cs::ExtendMerge* of = nullptr;
+      for (const auto& m : p.merges)
+        if (m.conv == t.conv && m.q0 == t.q0) of = &m;
+      CHECK(t.k0 == (of ? -1 - of->part0 : 0));
+    }
+    CHECK(!cs::chain_pays(whole, hkv, 256, 32, 1e6f));          // nothing is cut
+    CHECK(cs::chain_pays(p, hkv, 256, 1, 1e9f));                // the CUs are full of other work
   }
   CHECK(cut > 50);
 }
