@@ -457,15 +457,15 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
   }
 }
 
-// Merge of the pieces of one cut tile: one of 8 workgroups per (tile, kv head), 256 threads. Workgroup
-// `block` % 8 = w takes the rows of wave w, thread `tid` the accumulators of lane tid % 64, DT of its
+// Merge of the pieces of one cut tile: one of 8 workgroups per (tile, kv head), 256 threads; kv heads
+// fastest, as in the grid that wrote the records. Workgroup w takes the rows of wave w, thread `tid` the accumulators of lane tid % 64, DT of its
 // 4 DT groups of 4 dims; the pieces are added in their order (bitwise deterministic). A piece in which
 // a row sees no key has maximum -FLT_MAX and sum 0 and adds 0.
 template <int D, int G>
 __device__ __forceinline__ void extend_merge_body(const ExtendArgs& a, const int block, const int dl,
                                                   const int tid) {
   constexpr int DT = D / 32;
-  const int w = block % 8, g = (block / 8) % a.n_kv_heads;
+  const int g = block % a.n_kv_heads, w = (block / a.n_kv_heads) % 8;
   const ExtendMerge mg = a.merge(block / 8 / a.n_kv_heads);
   const ExtendConvDesc cd = a.conv(mg.conv);
   if (mg.q0 + 32 * (w / G) >= cd.q_len) return;   // rows past the chunk's end have no records
@@ -475,24 +475,43 @@ __device__ __forceinline__ void extend_merge_body(const ExtendArgs& a, const int
                      (static_cast<size_t>(mg.part0) * a.n_kv_heads + g) * extend_part_floats(D);
   const float* ml = rec + kExtendTileRows * D + (w * 64 + lane) * 2;
   const float* src = rec + ((w * 4 * DT + sub * DT) * 64 + lane) * 4;
+  // The first kAhead records are loaded whole before the maximum is known: one trip to memory less.
+  constexpr int kAhead = 4;
+  f32x2 x0[kAhead];
+  f32x4 v0[kAhead][DT];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) {
+    const size_t at = (i < mg.n_parts ? i : 0) * stride;
+    x0[i] = *reinterpret_cast<const f32x2*>(ml + at);
+#pragma unroll
+    for (int k = 0; k < DT; ++k) v0[i][k] = *reinterpret_cast<const f32x4*>(src + at + k * 256);
+  }
   float M = -FLT_MAX;
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) M = fmaxf(M, x0[i].x);
 #pragma unroll 4
-  for (int i = 0; i < mg.n_parts; ++i) M = fmaxf(M, ml[i * stride]);
+  for (int i = kAhead; i < mg.n_parts; ++i) M = fmaxf(M, ml[i * stride]);
   f32x4 acc[DT];
 #pragma unroll
   for (int k = 0; k < DT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
   float l = 0.f;
-#pragma unroll 4
-  for (int i = 0; i < mg.n_parts; ++i) {
-    const f32x2 x = *reinterpret_cast<const f32x2*>(ml + i * stride);
+  auto add = [&](f32x2 x, const f32x4 (&v)[DT]) {
     const float wt = fast_exp2(x.x - M);
     l = __builtin_fmaf(wt, x.y, l);
 #pragma unroll
-    for (int k = 0; k < DT; ++k) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(src + i * stride + k * 256);
+    for (int k = 0; k < DT; ++k)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[k][r] = __builtin_fmaf(wt, v[r], acc[k][r]);
-    }
+      for (int r = 0; r < 4; ++r) acc[k][r] = __builtin_fmaf(wt, v[k][r], acc[k][r]);
+  };
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i)
+    if (i < mg.n_parts) add(x0[i], v0[i]);
+#pragma unroll 2
+  for (int i = kAhead; i < mg.n_parts; ++i) {
+    f32x4 v[DT];
+#pragma unroll
+    for (int k = 0; k < DT; ++k) v[k] = *reinterpret_cast<const f32x4*>(src + i * stride + k * 256);
+    add(*reinterpret_cast<const f32x2*>(ml + i * stride), v);
   }
   const int qi = mg.q0 + 32 * (w / G) + (lane & 31);
   if (qi >= cd.q_len) return;
@@ -551,8 +570,7 @@ __global__ __launch_bounds__(256) void mixed_merge_kernel(ExtendArgs ea, int n_e
     extend_merge_body<D, G>(ea, blk, 0, threadIdx.x);
     return;
   }
-  const int nqh = da.n_kv_heads * G;
-  merge_body<D>(da, (blk - n_ext) / nqh, (blk - n_ext) % nqh, 0, threadIdx.x, lds);
+  merge_body<D>(da, blk - n_ext, 0, threadIdx.x, lds);
 }
 
 int extend_query_tile(int group) { return kExtendTileRows / group; }

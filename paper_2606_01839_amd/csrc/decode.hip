@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kDecodeItemThreads) void decode_split_kernel(Launch
 template <int D>
 __global__ __launch_bounds__(256) void decode_merge_kernel(LaunchMeta, DecodeArgs a) {
   __shared__ MergeLds<D> lds;
-  merge_body<D>(a, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x, lds);
+  merge_body<D>(a, blockIdx.x, blockIdx.y, threadIdx.x, lds);
 }
 
 hipError_t launch_decode_split(const PoolGeom& g, int layer, int n_layers, const DecodeLaunch& w, const void* q,
@@ -87,7 +87,7 @@ hipError_t launch_decode_merge(const PoolGeom& g, int n_layers, const DecodeLaun
   const DecodeArgs a = make_decode_args(g, 0, w, nullptr, out, partials);
   LaunchMeta m;
   fill_meta(w.meta, &m);
-  const dim3 grid(w.n_convs, g.n_q_heads, n_layers);
+  const dim3 grid(w.n_convs * g.n_q_heads, n_layers);
   if (g.head_dim == 128) decode_merge_kernel<128><<<grid, 256, 0, stream>>>(m, a);
   else if (g.head_dim == 64) decode_merge_kernel<64><<<grid, 256, 0, stream>>>(m, a);
   else return hipErrorInvalidValue;

@@ -80,11 +80,12 @@ def test_mixed_step_with_cut_tiles_equals_separate_calls(hq, hkv, d, ordered):
         b.close()
 
 
-@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 1, 64), (8, 8, 128)])
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 1, 64), (8, 8, 128), (4, 2, 128)])
 @pytest.mark.parametrize("lens", [[1025], [2047], [6000], [24571], [1100, 4096, 2500], [1500, 900]], ids=str)
 def test_decode_filling_splits_match_oracle(hq, hkv, d, lens):
     """Decode batches small enough to get splits of 32, 64 or 96 keys (and one that keeps its plan: it
-    holds a conversation of one item), with and without the allocation-free entry point."""
+    holds a conversation of one item), with and without the allocation-free entry point; 96 items a
+    conversation where few kv heads leave room, more than the merge loads ahead."""
     from paper_2606_01839_amd import KVPool
     pool = KVPool(1, hq, hkv, d, n_pages=sum((n + 15) // 16 for n in lens) + 8, max_convs=4, max_pages_per_conv=2048,
                   placement_seed=2, device="cuda")
