@@ -26,7 +26,7 @@ cs_status fail(cs_status code, const std::string& msg) {
 constexpr size_t kAlign = 256;
 constexpr size_t kRingBytes = size_t(8) << 20;  // metadata ring (device + pinned host), 4 quarters
 constexpr size_t kQuarter = kRingBytes / 4;
-constexpr int kMinSplit = 128;                   // smallest decode split: bounds the partials
+constexpr int kItemKeys = 128;  // the workspace has room for a decode record per this many keys (an item has 256 or more)
 // Splits (waves) a decode launch aims for (16 per CU). Half as many (longer splits, fewer items to
 // merge) made the 32-layer mixed trace 5% slower, twice as many 1% slower.
 constexpr int64_t kDecodeTargetItems = 4096;
@@ -49,8 +49,8 @@ struct WsLayout {
 };
 
 int64_t max_decode_items(const cs_pool_desc& d) {
-  // sum_b ceil(L_b / kMinSplit) <= total tokens / kMinSplit + batch
-  return d.n_pages * cs::kPage / kMinSplit + d.max_convs;
+  // sum_b ceil(L_b / kItemKeys) <= total tokens / kItemKeys + batch
+  return d.n_pages * cs::kPage / kItemKeys + d.max_convs;
 }
 
 WsLayout ws_layout(const cs_pool_desc& d) {
@@ -58,7 +58,7 @@ WsLayout ws_layout(const cs_pool_desc& d) {
   w.page_table = 0;
   size_t pt_bytes = static_cast<size_t>(d.max_convs) * static_cast<size_t>(d.max_pages_per_conv) * 4;
   w.partials = align_up(pt_bytes, kAlign);
-  const int64_t one_round = std::max(1, cs::kCus / d.n_kv_heads) * static_cast<int64_t>(d.n_layers);
+  const int64_t one_round = std::max(1, cs::kCus / d.n_kv_heads) * std::min<int64_t>(d.n_layers, 128);
   w.partial_floats = static_cast<size_t>(std::max(max_decode_items(d) * (d.n_layers > 1 ? 2 : 1), one_round)) *
                      d.n_q_heads * cs::partial_floats(d.head_dim);
   w.ext_parts = align_up(w.partials + w.partial_floats * 4, kAlign);

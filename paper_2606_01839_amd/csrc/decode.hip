@@ -3,8 +3,8 @@
 // A work item is up to kDecodeSubSplits splits (`split` keys each) of consecutive keys of one
 // (conversation, kv head), taken by one workgroup; its waves share its keys evenly, each reading
 // its range once and serving all G query heads of the kv head. Workgroups take the items in the
-// plan's launch order (full items first, then shorter ones). The two contractions per page pair are done on the matrix cores with
-// v_mfma_f32_16x16x32_bf16, the GQA group as the 16-wide N side:
+// plan's launch order (full items first, then shorter ones). The two contractions per page pair are
+// done on the matrix cores with v_mfma_f32_16x16x32_bf16, the GQA group as the 16-wide N side:
 //   S^T[key][head] = K[key][:] . Q[head][:]          (A = K rows straight from the page,
 //                                                     B = Q, 8 consecutive dims per lane)
 //   O^T[dim][head] += V^T[dim][key] . P^T[key][head]  (A = V^T rows from the page,
@@ -16,6 +16,9 @@
 // second kernel merges the items of each (conversation, query head). Both merges run in a fixed
 // order and there are no atomics: bitwise deterministic, and split boundaries are logical
 // positions, so results do not depend on physical page placement.
+// Bound: HBM in large batches (64 conversations of 8k-32k tokens: 6.7 TB/s, where a
+// plain streaming read of 4 GiB reaches 6.25), the four or fewer page pairs a wave reads one after the other and the merge
+// launch in small ones (one conversation of 2000 tokens 10.8 us, of 24.6k 20.6).
 #include <cmath>
 #include <mutex>
 
