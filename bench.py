@@ -554,7 +554,8 @@ def chunked_prefill(tr, lens, q, out_one_shot, mk, chunk=8192):
     conversation and attends it against the conversation's cached prefix (cs_attn_extend). Inputs
     of each round are staged before timing. Reports the attention and append kernel time, the
     wall time, and whether the output equals the one-shot prefill bit for bit (with 64-aligned
-    chunks the query tiles sweep the same key tiles in the same order)."""
+    chunks the query tiles sweep the same key tiles in the same order; a round with few enough tiles
+    to have their keys cut into pieces equals it to rounding only)."""
     sh = tr.shape
     hq, hkv, d = sh.n_q_heads, sh.n_kv_heads, sh.head_dim
     pool = mk(tr.seed + 7)

@@ -89,8 +89,8 @@ constexpr float kSumLimit = 256.f;
 // V^T page by page, D dims x 32 B (16 keys) per page, the two 16-byte halves of a dim swapped when
 // bit 2 xor bit 3 of the dim is set. A 16-byte operand read is served 16 lanes at a time over 256
 // bytes of banks: the 16 rows (K) or dims (V^T) such a group reads then fall in 16 distinct 16-byte
-// bank groups (rocprofv3 SQ_LDS_BANK_CONFLICT = 0), while every copy instruction still writes 1 KiB
-// of consecutive LDS bytes.
+// bank groups (rocprofv3 SQ_LDS_BANK_CONFLICT counts about 100 cycles a wave, those of the output rows
+// at the end), while every copy instruction still writes 1 KiB of consecutive LDS bytes.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lds_u32(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p));
