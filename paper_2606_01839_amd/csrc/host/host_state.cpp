@@ -174,6 +174,10 @@ ExtendPlan plan_extend(const std::vector<int32_t>& slots, const std::vector<int6
 constexpr float kStartSteps = 8.f;
 constexpr float kMergeSteps = 6.f;
 constexpr float kRecordSteps = 0.03f;
+// A launch that is this much longer for fewer pieces is preferred (513 tokens on 2948: 49 us in two pieces
+// a tile instead of 42.5 in three, but the 32-layer mixed step they arrive in 2.95 ms instead of 3.05;
+// uncut 79 us and 2.93 ms).
+constexpr float kFewerSteps = 6.f;
 
 // Time of workgroups of the given key tiles (longest first) on `slots` CUs.
 static float makespan(const std::vector<int32_t>& keys, int slots) {
@@ -208,12 +212,19 @@ void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t m
   std::sort(sorted.begin(), sorted.end(), std::greater<int32_t>());
   const int32_t longest = sorted[0];
   if (longest <= kMinPiece) return;
-  float best = 0.9f * makespan(sorted, slots);  // cut only for a clear gain
-  int32_t best_c = 0;
+  const float limit = 0.9f * makespan(sorted, slots);  // cut only for a clear gain
+  struct Cut {
+    int32_t c;
+    int parts;
+    float time;
+  };
+  std::vector<Cut> cuts;
   std::vector<int32_t> work_keys;
-  for (int rounds = 1; rounds <= 4; ++rounds) {
-    // the smallest size whose pieces fit in this many rounds of the CUs, and their records
-    int32_t c = std::max<int32_t>(kMinPiece, static_cast<int32_t>(total / (static_cast<int64_t>(rounds) * slots)));
+  // Sizes: the smallest whose pieces fit in one to four rounds of the CUs (and their records), and half
+  // the longest tile.
+  for (int rounds = 0; rounds <= 4; ++rounds) {
+    int32_t c = std::max<int32_t>(
+        kMinPiece, rounds == 0 ? (longest + 1) / 2 : static_cast<int32_t>(total / (static_cast<int64_t>(rounds) * slots)));
     c = (c + kPieceStep - 1) / kPieceStep * kPieceStep;
     int pieces = 0, parts = 0;
     for (;; c += std::max(1, c / 16 / kPieceStep) * kPieceStep) {
@@ -223,7 +234,7 @@ void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t m
         pieces += np;
         parts += np > 1 ? np : 0;
       }
-      if (c >= longest || (pieces <= rounds * slots && parts <= max_parts)) break;
+      if (c >= longest || (parts <= max_parts && (rounds == 0 || pieces <= rounds * slots))) break;
     }
     if (c >= longest) continue;
     work_keys.clear();
@@ -232,12 +243,19 @@ void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t m
       if (k % c) work_keys.push_back(k % c);
     std::sort(work_keys.begin(), work_keys.end(), std::greater<int32_t>());
     const float t = makespan(work_keys, slots) + kMergeSteps + kRecordSteps * static_cast<float>(parts * n_kv_heads);
-    if (t < best) {
-      best = t;
-      best_c = c;
-    }
+    if (t < limit) cuts.push_back({c, parts, t});
   }
-  if (best_c == 0) return;
+  if (cuts.empty()) return;
+  // Of the cuts within kFewerSteps of the best the one with the fewest pieces: beside a decode, which
+  // takes the CUs that cutting would fill, each piece only costs.
+  float best = limit;
+  for (const Cut& x : cuts) best = std::min(best, x.time);
+  const Cut* pick = nullptr;
+  for (const Cut& x : cuts)
+    if (x.time <= best + kFewerSteps && (pick == nullptr || x.parts < pick->parts ||
+                                         (x.parts == pick->parts && x.time < pick->time)))
+      pick = &x;
+  const int32_t best_c = pick->c;
   plan.piece = best_c;
   std::vector<std::pair<int32_t, ExtendTile>> work;
   for (int i = 0; i < n; ++i) {
