@@ -104,10 +104,14 @@ __device__ __forceinline__ void dma16(uint32_t lds, const void* gbase, uint32_t 
                : "=&s"(saved) : "s"(lds), "v"(voff), "s"(gbase) : "memory");
 }
 // Wait until at most N of this wave's vector-memory operations (its copies) are in flight, then a
-// workgroup barrier: afterwards every wave's copies issued before its own last N have landed.
-template <int N>
+// workgroup barrier: afterwards every wave's copies issued before its own last N have landed. A barrier
+// after which a buffer is copied over must also have that buffer's operand reads of every wave behind it,
+// and the matrix instructions that wait for them may be scheduled after the barrier: with READS the wave's
+// LDS reads return first.
+template <int N, bool READS = false>
 __device__ __forceinline__ void dma_wait_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N) : "memory");
+  if constexpr (READS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+  else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
 // One (tile or piece, kv head) workgroup (`block` = its index in the layer's grid, `dl` = its layer
@@ -357,8 +361,10 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
                                                          pop[kt2][j2], o[t], 0, 0, 0);
     if constexpr (PRE) read_k((buf + 1) % NBUF);      // tile j+1 is in LDS (waited at the end of step j-1)
     // this wave's copies of tile j+2 have landed (those of tile j+3 may still fly); after the
-    // barrier every wave's have.
-    dma_wait_barrier<2 * BPW>();
+    // barrier every wave's have. The next step copies over this step's buffer. With PRE its V^T operands
+    // were read before the softmax and the reads still in flight are the next tile's K, a buffer that is
+    // copied over a step later; without PRE the last V^T reads are waited for here.
+    dma_wait_barrier<2 * BPW, !PRE>();
   };
   // One piece's record: the accumulators as they lie in the registers (every store 1 KiB of consecutive
   // bytes per wave), then (maximum, sum) of each lane's row.

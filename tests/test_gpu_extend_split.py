@@ -99,3 +99,69 @@ def test_decode_filling_splits_match_oracle(hq, hkv, d, lens):
     for i in range(len(lens)):
         assert_close(out[i:i + 1], attend_last(f64(q[i:i + 1]), f64(kv[i][0][0]), f64(kv[i][1][0])), f"conv {i}")
     pool.close()
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (16, 8), (32, 8), (64, 8), (16, 2)])
+def test_head_dim_64_two_workgroups_a_cu(hq, hkv):
+    """A head_dim 64 launch of more than 640 workgroups takes the form without operand read-ahead. Its
+    first conversations alone stay below that and uncut (257 to 320 tiles at 2 kv heads, 65 to 80 at 8),
+    in the form that reads ahead: every row the same bits, and on other pages; sampled rows against the
+    oracle."""
+    d, tile, per = 64, 256 // (hq // hkv), 256 // hkv
+    first = [int(1.6 * per) * tile + 17, int(0.7 * per) * tile + 1]
+    lens = first + [per * tile + 3]
+    wg = [hkv * sum((n + tile - 1) // tile for n in x) for x in (first, lens)]
+    assert 512 < wg[0] <= 640 < wg[1]
+    kv = [kv_tokens(SEED, i, 1, 0, n, hkv, d, device="cuda") for i, n in enumerate(lens)]
+    q = torch.cat([q_tokens(SEED, i, 0, 0, n, hq, d, device="cuda") for i, n in enumerate(lens)])
+    out = _run(hq, hkv, d, [0] * 3, lens, 5, kv, q, True)
+    rows = sum(first)
+    assert torch.equal(out, _run(hq, hkv, d, [0] * 3, lens, 6, kv, q, True))
+    assert torch.equal(out[:rows], _run(hq, hkv, d, [0] * 2, first, 7, kv[:2], q[:rows].contiguous(), True))
+    row = 0
+    for i, n in enumerate(lens):
+        k, v = f64(kv[i][0][0]), f64(kv[i][1][0])
+        for r in np.unique(np.r_[0:3, np.linspace(0, n - 1, 12).astype(int)]):
+            ref = attend_last(f64(q[row + r:row + r + 1]), k[:r + 1], v[:r + 1])
+            assert_close(out[row + r:row + r + 1], ref, f"conv {i} row {r}")
+        row += n
+
+
+def _mixed_equals_separate(hq, hkv, d, layers, prefix, chunk, dec_lens, ordered):
+    """A mixed step of one chunk and the decoding conversations, and the separate calls on a second
+    pool: the same bits; sampled extend rows of the last layer against the oracle."""
+    from paper_2606_01839_amd import KVPool
+    lens, new = [prefix] + dec_lens, [chunk] + [1] * len(dec_lens)
+    pages = sum((n + m + 15) // 16 for n, m in zip(lens, new)) + 8
+    a, b = (KVPool(layers, hq, hkv, d, n_pages=pages, max_convs=len(lens), max_pages_per_conv=max(lens) // 16 + 80,
+                   placement_seed=s) for s in (8, 9))
+    ha, hb = ([p.conv_create() for _ in lens] for p in (a, b))
+    new_kv = []
+    for i, (n, m) in enumerate(zip(lens, new)):
+        k, v = kv_tokens(SEED, i, layers, 0, n + m, hkv, d, device="cuda")
+        for p, h in ((a, ha), (b, hb)):
+            p.kv_append(h[i], k[:, :n].contiguous(), v[:, :n].contiguous())
+        new_kv.append((k[:, n:].clone(), v[:, n:].clone()))
+        if i == 0:
+            k_ext, v_ext = f64(k[-1]), f64(v[-1])
+    k, v = (torch.cat([x[j] for x in new_kv], 1).contiguous() for j in (0, 1))
+    qe = torch.stack([q_tokens(SEED, 0, l, prefix, chunk, hq, d, device="cuda") for l in range(layers)])
+    qd = torch.stack([torch.cat([q_tokens(SEED, i + 1, l, n, 1, hq, d, device="cuda") for i, n in enumerate(dec_lens)])
+                      for l in range(layers)])
+    oe, od = a.mixed_step(ha[:1], [chunk], ha[1:], k, v, qe, qd, layer_ordered=ordered)
+    b.kv_append_batch(hb, new, k, v)
+    for l in range(layers):
+        assert torch.equal(oe[l], b.attn_extend(hb[:1], [chunk], l, qe[l])), l
+        assert torch.equal(od[l], b.attn_decode_batch(hb[1:], l, qd[l])), l
+    for r in np.unique(np.linspace(0, chunk - 1, 20).astype(int)):
+        ref = attend_last(f64(qe[-1, r:r + 1]), k_ext[:prefix + r + 1], v_ext[:prefix + r + 1])
+        assert_close(oe[-1, r:r + 1], ref, f"row {r}")
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("prefix,chunk", [(1200, 300), (1500, 500)])
+def test_chained_tiles_two_workgroups_a_cu(prefix, chunk):
+    """All layers of an overlapped head_dim 64 step in launches of more than 640 workgroups whose cut
+    tiles hold their pieces."""
+    _mixed_equals_separate(32, 8, 64, 24, prefix, chunk, [2100, 700], False)
