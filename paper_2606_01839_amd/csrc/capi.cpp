@@ -660,7 +660,6 @@ cs_status append_impl(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t
     m.bytes = b.bytes.size();
     if (st == CS_OK) st = launch(m, static_cast<int>(chunks.size()), c);
   } else {
-    if (carry_bytes > 0) st = upload(p, carry->bytes.data(), carry_bytes, carry_dev);
     const size_t per = kQuarter / sizeof(cs::PageChunk) - 1;
     for (size_t c0 = 0; c0 < chunks.size() && st == CS_OK; c0 += per) {
       const size_t c1 = std::min(chunks.size(), c0 + per);
@@ -669,6 +668,9 @@ cs_status append_impl(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t
       if (st == CS_OK)
         st = launch(meta_part(d, 0, (c1 - c0) * sizeof(cs::PageChunk)), static_cast<int>(c1 - c0), {});
     }
+    // After the chunks, which may go round the ring: nothing of it is reused before the launches that read
+    // the carried metadata are issued.
+    if (carry_bytes > 0 && st == CS_OK) st = upload(p, carry->bytes.data(), carry_bytes, carry_dev);
   }
   if (st != CS_OK) {
     roll_back();
