@@ -427,21 +427,22 @@ cs::ExtendLaunch push_extend(const cs::ExtendPlan& plan, size_t t0, size_t t1, B
   return e;
 }
 
-cs_status upload_extend(cs_pool* p, const cs::ExtendPlan& plan, ExtendWork* w) {
+// Tiles one part of a plan holds, beside its conversations (0: not even one).
+size_t extend_part_tiles(const cs::ExtendPlan& plan) {
   const size_t desc_bytes = align_up(plan.convs.size() * sizeof(cs::ExtendConvDesc), 16);
-  if (desc_bytes + kAlign + sizeof(cs::ExtendTile) > kQuarter)
-    return fail(CS_ENOMEM, "batch descriptor exceeds the metadata ring");
-  // (a plan with cut tiles is small: it stays in one part)
-  const size_t max_tiles = (kQuarter - desc_bytes - kAlign) / sizeof(cs::ExtendTile);
-  for (size_t t0 = 0; t0 < plan.tiles.size(); t0 += max_tiles) {
-    Blob b;
-    size_t off = 0;
-    cs::ExtendLaunch e = push_extend(plan, t0, std::min(plan.tiles.size(), t0 + max_tiles), &b, &off);
-    cs_status st = place_meta(p, b, &e.meta);
-    if (st != CS_OK) return st;
-    w->parts.push_back(e);
-    w->blobs.push_back(std::move(b));   // moving a vector keeps its buffer, which e.meta.host points to
-  }
+  if (desc_bytes + kAlign + sizeof(cs::ExtendTile) > kQuarter) return 0;
+  return (kQuarter - desc_bytes - kAlign) / sizeof(cs::ExtendTile);
+}
+
+// Tiles [t0, t1) of a plan as one more part of `w`.
+cs_status place_extend(cs_pool* p, const cs::ExtendPlan& plan, size_t t0, size_t t1, ExtendWork* w) {
+  Blob b;
+  size_t off = 0;
+  cs::ExtendLaunch e = push_extend(plan, t0, std::min(plan.tiles.size(), t1), &b, &off);
+  const cs_status st = place_meta(p, b, &e.meta);
+  if (st != CS_OK) return st;
+  w->parts.push_back(e);
+  w->blobs.push_back(std::move(b));   // moving a vector keeps its buffer, which e.meta.host points to
   return CS_OK;
 }
 
@@ -466,6 +467,21 @@ cs_status launch_extend_layers(cs_pool* p, const ExtendWork& w, int layer, int n
                              [&] { return cs::launch_extend_merge(g, nl, e, ol, p->ext_parts(), s); });
       if (st != CS_OK) return st;
     }
+  }
+  return CS_OK;
+}
+
+// Layers [0, n_layers) of a plan of any number of parts, each launched before the next is uploaded: the
+// ring holds four quarters, so a part that waited for the fourth after it would be gone.
+cs_status run_extend(cs_pool* p, const cs::ExtendPlan& plan, int layer, int n_layers, const void* q, void* out) {
+  const size_t per = extend_part_tiles(plan);
+  if (per == 0) return fail(CS_ENOMEM, "batch descriptor exceeds the metadata ring");
+  // (a plan with cut tiles is small: it stays in one part)
+  for (size_t t0 = 0; t0 < plan.tiles.size(); t0 += per) {
+    ExtendWork w;
+    cs_status st = place_extend(p, plan, t0, t0 + per, &w);
+    if (st == CS_OK) st = launch_extend_layers(p, w, layer, n_layers, q, out, p->stream);
+    if (st != CS_OK) return st;
   }
   return CS_OK;
 }
@@ -564,9 +580,7 @@ cs_status attend(cs_pool* p, int32_t n, const cs_conv* convs, const int32_t* q_l
     slots[i] = cs::ConvTable::slot_of(convs[i]);
     lens[i] = cv[i]->len;
   }
-  ExtendWork w;
-  if ((st = upload_extend(p, plan_extend_batch(p, slots, lens, ql), &w)) != CS_OK) return st;
-  return launch_extend_layers(p, w, layer, 1, q, out, p->stream);
+  return run_extend(p, plan_extend_batch(p, slots, lens, ql), layer, 1, q, out);
 }
 
 // Whether the conversations can take n_new[i] tokens each (nothing is changed); *total = their sum.
@@ -1014,7 +1028,13 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
     return st;
   if (n_dec > 0) dw.w.meta = meta_part(dev, d_off, d_bytes);
   if (e_carried) ew.parts[0].meta = meta_part(dev, e_off, blob.bytes.size() - e_off);
-  if (n_ext > 0 && !e_carried && (st = upload_extend(p, e_plan, &ew)) != CS_OK) return st;
+  // Up to three parts stay in the ring beside the carried plan until the last launch that reads them is
+  // issued; more are uploaded again where they are launched.
+  const size_t per = n_ext > 0 ? extend_part_tiles(e_plan) : 1;   // > 0: checked above
+  const bool e_held = e_carried || (e_plan.tiles.size() + per - 1) / per <= 3;
+  if (n_ext > 0 && !e_carried && e_held)
+    for (size_t t0 = 0; t0 < e_plan.tiles.size(); t0 += per)
+      if ((st = place_extend(p, e_plan, t0, t0 + per, &ew)) != CS_OK) return st;
   const size_t row_bytes = static_cast<size_t>(p->desc.n_q_heads) * p->desc.head_dim * 2;
   const int nl = p->desc.n_layers;
   const size_t ext_layer_bytes = static_cast<size_t>(ext_rows) * row_bytes;
@@ -1023,6 +1043,21 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
   auto o_e = [&](int l) { return static_cast<char*>(out_ext) + l * ext_layer_bytes; };
   auto q_d = [&](int l) { return static_cast<const char*>(q_dec) + l * dec_layer_bytes; };
   auto o_d = [&](int l) { return static_cast<char*>(out_dec) + l * dec_layer_bytes; };
+  if (!e_held) {
+    // More metadata than the ring holds (100,000 chunks and more): everything on one stream, the decode
+    // first, whose carried plan the parts of the extend plan go over; in layer order it is uploaded again.
+    if (!(flags & CS_MIXED_LAYER_ORDERED)) {
+      if (n_dec > 0) st = launch_decode_layers(p, dw, 0, nl, q_d(0), o_d(0));
+      return st != CS_OK ? st : run_extend(p, e_plan, 0, nl, q_e(0), o_e(0));
+    }
+    for (int layer = 0; layer < nl && st == CS_OK; ++layer) {
+      DecodeWork again;
+      if (n_dec > 0) st = place_decode(p, d_plan, &again);
+      if (n_dec > 0 && st == CS_OK) st = launch_decode_layers(p, again, layer, 1, q_d(layer), o_d(layer));
+      if (st == CS_OK) st = run_extend(p, e_plan, layer, 1, q_e(layer), o_e(layer));
+    }
+    return st;
+  }
   // Extend chunks and decode tokens are independent once their K/V is appended: with both present
   // the extend launches go to a second stream (forked from `stream`, joined back before the call
   // returns), so the matrix-core-bound extend work overlaps the HBM-bound decode work.
