@@ -36,6 +36,10 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kMaxLayersPerLaunch = 32768;  // a grid dimension
 // Records of cut extend tiles one layer may write: two per CU.
 constexpr int kExtendRecords = 2 * cs::kCus;
+// Tiles and merges of a plan that split_extend has cut: at most two rounds of tiles, each a tile or a
+// merge, and a piece for every record.
+constexpr size_t kMaxCutBytes = 2 * cs::kCus * (sizeof(cs::ExtendTile) + sizeof(cs::ExtendMerge)) +
+                                kExtendRecords * sizeof(cs::ExtendTile) + kAlign;
 // Records the workspace holds (68 MB at head dim 128; 203 MB in a multi-layer pool, whose overlapped
 // steps put as many layers into one launch as have room: 28 layers of a 4-conversation step in one
 // launch instead of three 395 -> 374 us, 32 of an 8-conversation one 1614 -> 1527 us).
@@ -407,7 +411,10 @@ cs::ExtendPlan plan_extend_batch(const cs_pool* p, const std::vector<int32_t>& s
                                  const std::vector<int64_t>& lens, const std::vector<int32_t>& q_lens) {
   const int tile = cs::extend_query_tile(p->desc.n_q_heads / p->desc.n_kv_heads);
   cs::ExtendPlan plan = cs::plan_extend(slots, lens, q_lens, tile);
-  cs::split_extend(plan, p->desc.n_kv_heads, cs::kCus, kExtendRecords);
+  // A cut plan is one part: a part's merges follow its launch and read every piece of their tiles. Beside
+  // the descriptors of some 129,000 conversations (nearly all without queries) there is no room for it.
+  if (plan.convs.size() * sizeof(cs::ExtendConvDesc) + kMaxCutBytes <= kQuarter)
+    cs::split_extend(plan, p->desc.n_kv_heads, cs::kCus, kExtendRecords);
   return plan;
 }
 
@@ -476,7 +483,6 @@ cs_status launch_extend_layers(cs_pool* p, const ExtendWork& w, int layer, int n
 cs_status run_extend(cs_pool* p, const cs::ExtendPlan& plan, int layer, int n_layers, const void* q, void* out) {
   const size_t per = extend_part_tiles(plan);
   if (per == 0) return fail(CS_ENOMEM, "batch descriptor exceeds the metadata ring");
-  // (a plan with cut tiles is small: it stays in one part)
   for (size_t t0 = 0; t0 < plan.tiles.size(); t0 += per) {
     ExtendWork w;
     cs_status st = place_extend(p, plan, t0, t0 + per, &w);

@@ -3,7 +3,8 @@ that read it are still to be issued."""
 import pytest
 import torch
 
-from tests.helpers import kv_tokens, q_tokens
+from oracle.attention import attend_last
+from tests.helpers import assert_close, f64, kv_tokens, q_tokens
 
 pytestmark = pytest.mark.gpu
 
@@ -72,4 +73,22 @@ def test_mixed_step_of_more_tiles_than_the_ring_holds(n, ordered):
     pool.mixed_step(convs, [1] * n, dec, k, v, qe[None], qd[None], oe, od, layer_ordered=ordered)
     assert torch.equal(oe[0], v[0, :n])
     assert torch.equal(od[0], pool.attn_decode_batch(dec, 0, qd))
+    pool.close()
+
+
+@pytest.mark.parametrize("n,hkv", [(129_000, 1), (130_900, 1), (131_055, 1), (131_055, 2)])
+def test_long_chunk_beside_descriptors_that_fill_a_quarter(n, hkv):
+    """One 1500-row chunk of 3000 tokens, which alone is cut into pieces and 24 merges, in a batch whose
+    other conversations have no queries but a descriptor each: up to the largest batch a quarter of the
+    ring can describe, where one tile fits beside them."""
+    from paper_2606_01839_amd import KVPool
+    d, L, c = 64, 3000, 1500
+    pool = KVPool(1, 4 * hkv, hkv, d, n_pages=256, max_convs=n, max_pages_per_conv=256, placement_seed=3, device="cuda")
+    convs = [pool.conv_create() for _ in range(n)]
+    at = n // 2
+    k, v = kv_tokens(SEED, 0, 1, 0, L, hkv, d)
+    pool.kv_append(convs[at], k.cuda(), v.cuda())
+    q = q_tokens(SEED, 0, 0, L - c, c, 4 * hkv, d)
+    out = pool.attn_extend(convs, [c if i == at else 0 for i in range(n)], 0, q.cuda())
+    assert_close(out, attend_last(f64(q), f64(k[0]), f64(v[0])), f"{n} descriptors")
     pool.close()
