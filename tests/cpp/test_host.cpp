@@ -1,6 +1,7 @@
 // Host-metadata unit test (page pool, conversation table, plans); built with -fsanitize=address,
 // undefined by tests/test_host_cpp.py. Exits non-zero on the first failed check.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -255,6 +256,37 @@ static void extend_split_random() {
   CHECK(cut > 50);
 }
 
+// Deciding that a launch is not cut costs less than planning its tiles (it is before every launch, and
+// once for each layer of a layer by layer caller): the best of 20 runs each of a few uncut launches.
+static void extend_split_cost() {
+  struct Launch {
+    int hkv, q_tile, n;
+    int64_t len, step;
+    int32_t q;
+  };
+  for (const Launch& x : {Launch{2, 32, 1, 8000, 0, 8000}, {2, 32, 256, 300, 1, 30}, {1, 32, 500, 900, 3, 30}}) {
+    std::vector<int32_t> slots(x.n), ql(x.n, x.q);
+    std::vector<int64_t> lens(x.n);
+    for (int i = 0; i < x.n; ++i) {
+      slots[i] = i;
+      lens[i] = x.len + i * x.step;
+    }
+    double plan_s = 1e9, split_s = 1e9;
+    for (int run = 0; run < 20; ++run) {
+      const auto t0 = std::chrono::steady_clock::now();
+      cs::ExtendPlan p = cs::plan_extend(slots, lens, ql, x.q_tile);
+      const auto t1 = std::chrono::steady_clock::now();
+      cs::split_extend(p, x.hkv, 256, 512);
+      const auto t2 = std::chrono::steady_clock::now();
+      CHECK(p.merges.empty());
+      plan_s = std::min(plan_s, std::chrono::duration<double>(t1 - t0).count());
+      split_s = std::min(split_s, std::chrono::duration<double>(t2 - t1).count());
+    }
+    if (split_s >= plan_s) std::fprintf(stderr, "%d tiles: plan %.1f us, split %.1f us\n", x.n, plan_s * 1e6, split_s * 1e6);
+    CHECK(split_s < plan_s);
+  }
+}
+
 static void append_plan() {
   std::vector<int32_t> pages0 = {7, 3};        // conversation with 20 tokens (2 pages) + 1 new
   std::vector<int32_t> pages1 = {5};           // empty conversation receiving 16 tokens
@@ -310,6 +342,7 @@ int main() {
   decode_plan_filling();
   extend_plan();
   extend_split_random();
+  extend_split_cost();
   append_plan();
   std::puts("host metadata tests passed");
   return 0;
