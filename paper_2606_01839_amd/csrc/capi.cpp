@@ -1003,16 +1003,9 @@ cs_status cs_mixed_step(cs_pool* p, int32_t n_ext, const cs_conv* ext_convs, con
   }
   cs::ExtendPlan e_plan = plan_extend_batch(p, e_slots, e_lens, e_q);
   const bool ordered = (flags & CS_MIXED_LAYER_ORDERED) != 0;
-  {
-    // The decode's share of the CUs, in steps of one key tile (1.3 us on a busy chip): its K and V at
-    // 6 TB/s.
-    double dec_tokens = 0;
-    for (int64_t L : d_lens) dec_tokens += static_cast<double>(L);
-    const double dec_us = dec_tokens * p->desc.n_kv_heads * p->desc.head_dim * 4 / 6e6;
-    const float dec_steps = static_cast<float>(dec_us / 1.3 * std::max(1, cs::kCus / p->desc.n_kv_heads));
-    if (cs::chain_pays(e_plan, p->desc.n_kv_heads, cs::kCus, ordered ? 1 : p->desc.n_layers, dec_steps))
-      cs::chain_extend(e_plan);
-  }
+  const float dec_steps = cs::decode_steps(d_lens, p->desc.n_kv_heads, p->desc.head_dim, cs::kCus);
+  if (cs::chain_pays(e_plan, p->desc.n_kv_heads, cs::kCus, ordered ? 1 : p->desc.n_layers, dec_steps))
+    cs::chain_extend(e_plan);
   Blob blob;
   ExtendWork ew;
   DecodeWork dw;

@@ -315,6 +315,13 @@ void chain_extend(ExtendPlan& plan) {
   plan.merges.clear();
 }
 
+float decode_steps(const std::vector<int64_t>& lens, int32_t n_kv_heads, int32_t head_dim, int32_t n_cus) {
+  double tokens = 0;
+  for (int64_t L : lens) tokens += static_cast<double>(L);
+  const double us = tokens * n_kv_heads * head_dim * 4 / 6e6;
+  return static_cast<float>(us / 1.3 * std::max(1, n_cus / n_kv_heads));
+}
+
 bool chain_pays(const ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t n_layers, float other_steps) {
   if (plan.merges.empty()) return false;
   const float slots = static_cast<float>(std::max(1, n_cus / n_kv_heads));

@@ -178,6 +178,10 @@ void split_extend(ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t m
 // their merge launch and most of their records' way to memory).
 void chain_extend(ExtendPlan& plan);
 
+// A decode batch's share of the CUs in steps of one key tile of the attention kernel (1.3 us on a busy chip
+// at head dim 128), for each layer and kv head: its K and V at 6 TB/s.
+float decode_steps(const std::vector<int64_t>& lens, int32_t n_kv_heads, int32_t head_dim, int32_t n_cus);
+
 // Whether chain_extend makes the launch shorter where other work waits for the CUs too: other_steps of
 // it for each layer and kv head (in CU-steps of a key tile), n_layers layers in the launch.
 bool chain_pays(const ExtendPlan& plan, int32_t n_kv_heads, int32_t n_cus, int32_t n_layers, float other_steps);

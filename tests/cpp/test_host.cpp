@@ -256,6 +256,51 @@ static void extend_split_random() {
   CHECK(cut > 50);
 }
 
+// What the GPU tests of cut and chained tiles rely on: which of their launches are cut, hold chained
+// tiles, or take more than 640 workgroups.
+static void extend_plans_of_gpu_tests() {
+  // test_cut_tiles_match_oracle: pieces for each head shape and (prefixes, chunks)
+  const int shapes[9][2] = {{32, 8}, {16, 8}, {64, 8}, {8, 8}, {2, 1}, {4, 2}, {32, 8}, {16, 2}, {4, 4}};
+  const std::vector<std::vector<int32_t>> prefix = {{4000}, {4095}, {5000}, {100}, {0}, {3000}, {2000, 10, 1300, 0}},
+                                          chunk = {{1}, {2}, {65}, {1437}, {1437}, {300}, {40, 130, 7, 64}};
+  const int parts[9][7] = {{8, 9, 20, 0, 0, 24, 7},    {8, 9, 10, 24, 20, 21, 7},   {8, 9, 30, 0, 0, 20, 11},
+                           {8, 9, 10, 14, 6, 14, 7},   {8, 9, 10, 24, 12, 21, 7},   {8, 9, 10, 24, 12, 21, 7},
+                           {8, 9, 20, 0, 0, 24, 7},    {8, 9, 30, 84, 71, 68, 11},  {8, 9, 10, 14, 6, 14, 7}};
+  for (int s = 0; s < 9; ++s)
+    for (int z = 0; z < 7; ++z) {
+      std::vector<int32_t> slots;
+      std::vector<int64_t> lens;
+      for (size_t i = 0; i < prefix[z].size(); ++i) {
+        slots.push_back(static_cast<int32_t>(i));
+        lens.push_back(prefix[z][i] + chunk[z][i]);
+      }
+      cs::ExtendPlan p = cs::plan_extend(slots, lens, chunk[z], 256 / (shapes[s][0] / shapes[s][1]));
+      cs::split_extend(p, shapes[s][1], 256, 512);
+      CHECK(p.n_parts == parts[s][z]);
+    }
+  // mixed steps of one chunk: tiles held whole or as chained pieces, and the workgroups of the layers of a
+  // launch (three times 512 records in a multi-layer pool)
+  struct Step {
+    int hq, hkv, d, layers;  // layers: of the plan, 1 in layer order
+    int32_t prefix, chunk;
+    std::vector<int64_t> dec;
+    bool chained, over_640;
+  };
+  const std::vector<int64_t> few = {2101, 701}, many(12, 8001);
+  for (const Step& x : {Step{32, 8, 64, 24, 1200, 300, few, true, true}, {32, 8, 64, 24, 1500, 500, few, true, true},
+                        {32, 8, 128, 1, 1200, 300, many, true, false}, {16, 8, 128, 1, 1200, 300, many, true, false},
+                        {32, 8, 64, 1, 1200, 300, many, true, false}, {32, 8, 128, 1, 2500, 90, few, false, false}}) {
+    cs::ExtendPlan p = cs::plan_extend({0}, {x.prefix + x.chunk}, {x.chunk}, 256 / (x.hq / x.hkv));
+    cs::split_extend(p, x.hkv, 256, 512);
+    CHECK(p.n_parts > 0);
+    const bool pays = cs::chain_pays(p, x.hkv, 256, x.layers, cs::decode_steps(x.dec, x.hkv, x.d, 256));
+    CHECK(pays == x.chained);
+    if (pays) cs::chain_extend(p);
+    const int per = std::min(x.layers, 3 * 512 / (p.n_parts * x.hkv));
+    CHECK((static_cast<int>(p.tiles.size()) * x.hkv * per > 640) == x.over_640);
+  }
+}
+
 // Deciding that a launch is not cut costs less than planning its tiles (it is before every launch, and
 // once for each layer of a layer by layer caller): the best of 20 runs each of a few uncut launches.
 static void extend_split_cost() {
@@ -342,6 +387,7 @@ int main() {
   decode_plan_filling();
   extend_plan();
   extend_split_random();
+  extend_plans_of_gpu_tests();
   extend_split_cost();
   append_plan();
   std::puts("host metadata tests passed");

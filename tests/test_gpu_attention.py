@@ -213,9 +213,10 @@ def test_chunked_extend_matches_one_shot_prefill():
 @pytest.mark.parametrize("hq,hkv", [(32, 8), (16, 8)])
 def test_aligned_chunked_prefill_is_bitwise_one_shot(hq, hkv):
     """Chunked turn-1 prefill (the prefiller's chunked prefill, Section 5.1) with chunks that are
-    multiples of the query tile (64 queries at 32q/8kv, 128 at 16q/8kv): every query tile sweeps
-    the same key tiles in the same order as in the one-shot prefill, so the outputs agree bit for
-    bit (and both match the oracle)."""
+    multiples of the query tile (64 queries at 32q/8kv, 128 at 16q/8kv): where no launch cuts its
+    tiles' keys into pieces, as with these short prompts, every query tile sweeps the same key tiles
+    in the same order as in the one-shot prefill, so the outputs agree bit for bit (and both match
+    the oracle)."""
     d = 128
     lens, chunk = [700, 300], 256
     pool = _pool(hq, hkv, d, 2 * sum((L + 15) // 16 for L in lens) + 8)

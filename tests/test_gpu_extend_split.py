@@ -165,3 +165,9 @@ def test_chained_tiles_two_workgroups_a_cu(prefix, chunk):
     """All layers of an overlapped head_dim 64 step in launches of more than 640 workgroups whose cut
     tiles hold their pieces."""
     _mixed_equals_separate(32, 8, 64, 24, prefix, chunk, [2100, 700], False)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (16, 8, 128), (32, 8, 64)])
+def test_chained_tiles_in_layer_order(hq, hkv, d):
+    """A layer's launch beside a decode large enough that one workgroup takes a cut tile's pieces."""
+    _mixed_equals_separate(hq, hkv, d, 2, 1200, 300, [8000] * 12, True)

@@ -94,9 +94,9 @@ def test_mixed_step_rejects_overlap_without_changes():
 def test_mixed_step_bitwise_equals_per_layer_calls(n_layers, layer_ordered, shape):
     """The mixed step gives bit for bit the outputs of the separate calls (kv_append_batch, then
     attn_extend and attn_decode_batch layer by layer, on a second pool with the same placement),
-    both with all layers overlapped (one launch per layer that merges layer l-1 and splits layer l,
-    alternating two partial buffers) and in layer order (at d 64 the fork/join form). Decode-only
-    and extend-only steps included; the last layer's decode outputs are checked against the oracle."""
+    both with all layers overlapped (the extend and the decode work of all layers in one launch each)
+    and in layer order (one launch for each layer, and one that merges). Decode-only and extend-only
+    steps included; the last layer's decode outputs are checked against the oracle."""
     from paper_2606_01839_amd import KVPool
     hq, hkv, d = shape
     mk = lambda: KVPool(n_layers, hq, hkv, d, n_pages=900, max_convs=8, max_pages_per_conv=256,
