@@ -59,24 +59,22 @@ template <int D>
 constexpr int split_exchange_floats() { return (kDecodeSubSplits - 1) * 8 * (D + 2); }
 
 // `dl` = layer of the launch, counted from a.layer.
-// Work unit `work` = (order[work / n_kv_heads], work % n_kv_heads) = (item, kv head) of the plan,
-// taken by one workgroup of kDecodeSubSplits waves (this wave = `wave`; `xch` = its LDS exchange
+// Work unit `work` < n_items * n_kv_heads, that is (order[work / n_kv_heads], work % n_kv_heads) =
+// (item, kv head) of the plan, taken by one workgroup of kDecodeSubSplits waves (this wave = `wave`; `xch` = its LDS exchange
 // area, split_exchange_floats<D>() floats). The item's n keys are shared out evenly: wave w reads
 // keys [k0 + w s, k0 + (w + 1) s) with s = ceil(n / kDecodeSubSplits) rounded up to a page pair,
 // so a short last item keeps all its waves busy for a short time instead of a few of them for a
 // full split. Then the other waves hand their (o, m, l) to wave 0 through LDS, which merges them
 // in the order w = 0, 1, ... and writes the item's one partial record: far fewer, larger writes
 // interleaved with the KV stream than one record per wave (the HBM reads run 7% faster with 8
-// waves per item than with one). Every wave reaches the one barrier, also in a workgroup whose
-// work unit lies past the end (work >= n_items * n_kv_heads: no keys, nothing written).
+// waves per item than with one). Every wave reaches the one barrier, also one that has no keys.
 template <int D>
 __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, const int dl, const int wave,
                                            float* xch) {
   constexpr int KS = D / 32;  // k-steps of the QK^T contraction
   constexpr int DT = D / 16;  // 16-dim tiles of the output
   const int lane = threadIdx.x & 63;
-  const bool valid = work < a.n_items * a.n_kv_heads;
-  const int item = a.order()[valid ? work / a.n_kv_heads : 0], g = work % a.n_kv_heads;
+  const int item = a.order()[work / a.n_kv_heads], g = work % a.n_kv_heads;
   const auto* convs = a.convs();
   const int conv_idx = find_conv(convs, a.n_convs, item);
   const DecodeConvDesc cd = load_desc(convs + conv_idx);
@@ -85,7 +83,7 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
   const int wave_keys = ((item_k1 - item_k0 + kDecodeSubSplits - 1) / kDecodeSubSplits + 2 * kPageTokens - 1) &
                         ~(2 * kPageTokens - 1);  // <= split (a multiple of 32)
   const int k_begin = item_k0 + wave * wave_keys;
-  const int k_end = valid ? min(item_k1, k_begin + wave_keys) : k_begin;
+  const int k_end = min(item_k1, k_begin + wave_keys);
   const int n_pg = k_end > k_begin ? (k_end - k_begin + kPageTokens - 1) / kPageTokens : 0;
   const int32_t* pt = a.page_table + static_cast<size_t>(cd.slot) * a.max_pages + k_begin / kPageTokens;
 
@@ -207,7 +205,7 @@ __device__ __forceinline__ void split_body(const DecodeArgs& a, const int work, 
     }
   }
   __syncthreads();
-  if (wave == 0 && valid && c < a.group) {
+  if (wave == 0 && c < a.group) {
     // wave 0 always holds keys, so M is finite; merge in the order w = 0, 1, ...
     float M = m_run;
 #pragma unroll
