@@ -82,8 +82,9 @@ typedef struct {
  */
 size_t cs_pool_kv_bytes(const cs_pool_desc* desc);
 
-/* Device workspace bytes the pool needs (page-table mirror, decode partials, records of extend tiles
- * whose keys are cut into pieces, metadata ring). */
+/* Device workspace bytes the pool needs: page-table mirror, decode partials, records of extend tiles
+ * whose keys are cut into pieces (head_dim 128: 69 MB, 208 MB in a pool of several layers; about half at
+ * 64; none where no conversation can exceed 512 tokens), metadata ring (8 MiB). */
 size_t cs_pool_workspace_bytes(const cs_pool_desc* desc);
 
 /*
@@ -142,6 +143,11 @@ cs_status cs_kv_append_batch(cs_pool* pool, int32_t n_convs, const cs_conv* conv
  * q_lens[i] must equal its length (its whole content is the prompt just appended).
  * q:   device [sum(q_lens)][n_q_heads][head_dim] bf16, conversations in batch order.
  * out: device, same shape; bf16 (round to nearest even) of softmax(q k^T / sqrt(d)) v, causal.
+ * The result is bitwise deterministic and independent of physical page placement. It depends on the
+ * call's batch as far as rounding goes: a call with few queries cuts the keys into pieces, whose size
+ * follows from the whole batch, and sums them piece by piece. The same queries in another batch, or
+ * chunk by chunk, agree to the rounding of bf16 weights (measured: 3e-3 in the 2-norm), and bit for bit
+ * only where neither call cuts its keys.
  * Errors: CS_EINVAL (null, duplicate conv, q_len < 0), CS_ENOENT, CS_ESTATE (q_len != length),
  * CS_ERANGE (layer), CS_ENOMEM (metadata larger than the ring), CS_EHIP.
  */
@@ -153,7 +159,8 @@ cs_status cs_attn_prefill_turn1(cs_pool* pool, int32_t n_convs, const cs_conv* c
  * Extend-prefill of a later turn (Section 3.1 "prefix caching": the appended tokens attend to the
  * whole cached history and causally among themselves; Section 4: it runs on the pinned decoder).
  * Same arguments as cs_attn_prefill_turn1 but 0 <= q_lens[i] <= length (q_len == length is a full
- * prefill, q_len == 1 a decode). Errors as above, CS_ESTATE when q_len > length.
+ * prefill, q_len == 1 a decode), and the same holds for its bits. Errors as above, CS_ESTATE when
+ * q_len > length.
  */
 cs_status cs_attn_extend(cs_pool* pool, int32_t n_convs, const cs_conv* convs,
                          const int32_t* q_lens, int32_t layer, const void* q, void* out,
@@ -201,17 +208,19 @@ cs_status cs_attn_decode_batch_noalloc(cs_pool* pool, int32_t n_convs, const cs_
  *   k, v:     [n_layers][sum(ext_lens) + n_dec][n_kv_heads][head_dim], extend tokens first
  *   q_ext:    [n_layers][sum(ext_lens)][n_q_heads][head_dim];  out_ext same shape
  *   q_dec:    [n_layers][n_dec][n_q_heads][head_dim];          out_dec same shape
- * The batch metadata is uploaded once and reused by every layer's launches. When both parts are
- * present, the extend launches run on a second stream owned by the pool, forked from `stream`
- * after the append and joined back into it before the call returns: work enqueued on `stream`
- * afterwards (and a synchronisation of `stream`) sees every output of the step.
+ * The batch metadata is uploaded once and reused by every layer's launches. Work enqueued on
+ * `stream` after the call (and a synchronisation of `stream`) sees every output of the step.
  * flags = 0: every layer's queries are inputs of the call, so no layer waits for another: the extend
  *   work of all layers is one launch and the decode work of all layers another (several where the
- *   workspace has no room for the records of all layers), beside each other, each followed by its merge.
+ *   workspace has no room for the records of all layers), each followed by its merge. With both parts
+ *   present the extend launches run beside the decode on a second stream owned by the pool, forked
+ *   from `stream` after the append and joined back into it before the call returns.
  * flags = CS_MIXED_LAYER_ORDERED: the order of a model forward pass, where layer l+1's queries
  *   depend on layer l's output: layer l's extend and decode overlap each other, and layer l+1
  *   starts only when both are complete. With both parts present a layer is one launch holding its
  *   extend tiles and its decode split, then one that merges what they left in pieces.
+ * (Extend plans larger than a 2 MiB upload -- some 65,000 chunks or more -- take the second stream in
+ * layer order too; larger than three uploads, everything runs on `stream`.)
  * Outputs are bitwise the same either way (and the same as the separate calls).
  * Errors: as cs_kv_append_batch, cs_attn_extend and cs_attn_decode_batch; CS_EINVAL for unknown
  * flags.

@@ -227,8 +227,9 @@ __device__ __forceinline__ void attn_fwd_block(const ExtendArgs& a, const int bl
   for (int i = 0; i < 3; ++i) copy_tile(__builtin_amdgcn_readlane(pages, i), i);
   int page_next = __builtin_amdgcn_readlane(pages, 3);
   __builtin_amdgcn_sched_barrier(0);   // no wait for Q before the copies are issued
-  // Q must have arrived before the loop: the compiler's own vector-memory waits then never
-  // extend to the copies the loop keeps in flight (a wait at the loop head would drain them).
+  // Q must have arrived before the loop: a wait of the compiler's at the loop head would drain the copies
+  // that the loop keeps in flight. Here too its waits do not count the copies (made in asm) and so wait
+  // for all three tiles behind Q, though the barrier below needs only two.
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     if (!valid) qop[ks] = bf16x8{};
@@ -556,8 +557,9 @@ __global__ __launch_bounds__(256) void extend_merge_kernel(LaunchMeta, ExtendArg
 
 // One layer of a mixed step in one launch: extend tiles (or pieces) and work items of the decode split
 // (8 waves, as in the split kernel), one workgroup each. Every workgroup gets the attention kernel's LDS
-// ring and register budget (two waves per SIMD); the decode split reads HBM as fast with two waves per
-// SIMD as with three.
+// ring and register budget, one workgroup (two waves per SIMD) a CU; at head dim 128 the decode split has no
+// more by itself. At 64 it has three workgroups a CU by itself: 16 conversations of 10k tokens and a 20-token
+// chunk take 64 us a layer here, 61 with the decode in its own launch.
 // Units of n_kv_heads workgroups are taken in an order that spreads the extend units evenly over the
 // first n_mix units, so that at any time some CUs use the matrix cores while others read HBM; n_mix =
 // their number puts them all in front (tiles longer than everything else).

@@ -40,7 +40,7 @@ constexpr int kExtendRecords = 2 * cs::kCus;
 // merge, and a piece for every record.
 constexpr size_t kMaxCutBytes = 2 * cs::kCus * (sizeof(cs::ExtendTile) + sizeof(cs::ExtendMerge)) +
                                 kExtendRecords * sizeof(cs::ExtendTile) + kAlign;
-// Records the workspace holds (68 MB at head dim 128; 203 MB in a multi-layer pool, whose overlapped
+// Records the workspace holds (69 MB at head dim 128; 208 MB in a multi-layer pool, whose overlapped
 // steps put as many layers into one launch as have room: 28 layers of a 4-conversation step in one
 // launch instead of three 395 -> 374 us, 32 of an 8-conversation one 1614 -> 1527 us).
 int extend_records(const cs_pool_desc& d) { return (d.n_layers > 1 ? 3 : 1) * kExtendRecords; }

@@ -16,9 +16,10 @@
 // second kernel merges the items of each (conversation, query head). Both merges run in a fixed
 // order and there are no atomics: bitwise deterministic, and split boundaries are logical
 // positions, so results do not depend on physical page placement.
-// Bound: HBM in large batches (64 conversations of 8k-32k tokens: 6.7 TB/s, where a
-// plain streaming read of 4 GiB reaches 6.25), the four or fewer page pairs a wave reads one after the other and the merge
-// launch in small ones (one conversation of 2000 tokens 10.8 us, of 24.6k 20.6).
+// Bound: HBM in large batches (64 conversations of 8k-32k tokens: 6.74 TB/s, 95% of the 7.07 that the
+// fastest plain read of 4 GiB in 8 KiB blocks reaches); in small ones the four or fewer page pairs a wave
+// reads one after the other and the merge launch (one conversation of 2000 tokens 11.3 us, of 24.6k 19.1
+// of which the merge is 3.9).
 #include <cmath>
 #include <mutex>
 

@@ -170,7 +170,11 @@ ExtendPlan plan_extend(const std::vector<int32_t>& slots, const std::vector<int6
 // tile (1.16 us at head dim 128 on a part-filled chip): the CUs one kv head gets (n_cus / n_kv_heads) take
 // the workgroups longest first; each costs its key tiles plus kStartSteps (measured 9 us: plan, pages,
 // queries and first tiles one after the other from memory, the refresh of the first tile's maximum, the
-// last stores), and cutting costs the merge launch plus the records' way to memory and back.
+// last stores), and cutting costs the merge launch plus the records' way to memory and back. The same
+// numbers serve head dim 64, where a step is shorter against start-up and merge: of 93 launches (prompts
+// of 300 to 9000 tokens, chunks of 1 to 1000 on 600 to 20,000) none is slower than with whole tiles and 59
+// are 1.2 to 10 times faster; of 24 layer-ordered steps beside a decode three are slower, by 1, 2 and 5%,
+// all with 1000-token chunks.
 constexpr float kStartSteps = 8.f;
 constexpr float kMergeSteps = 6.f;
 constexpr float kRecordSteps = 0.03f;

@@ -113,11 +113,12 @@ DecodePlan plan_decode(const std::vector<int32_t>& slots, const std::vector<int6
 
 // The same, but a batch whose work items (over all kv heads) would leave CUs without one gets the
 // smallest splits, in steps of a page pair, whose items still fit the CUs in one round: one
-// conversation of 2000 tokens 17.1 -> 12.4 us, 6000 (24 items instead of 6) 18.3 -> 12.4, four of
-// 1000-4000 19.2 -> 14.5; a second round that is not full costs more than it gives (24.6k tokens as 48
-// items of 64-key splits 26.3 us, as 24 of 128 23.2). A batch with a conversation of one item keeps its
-// plan: where all are, the split writes the outputs without a merge (600 tokens 9.7 us, cut 12.3), and
-// such a conversation's bits do not depend on the batch it is decoded in.
+// conversation of 2000 tokens 14.2 -> 11.3 us, 6000 (24 items instead of 6) 15.1 -> 11.1, four of
+// 1100-4000 18.1 -> 13.1, 24.6k 20.3 -> 19.1; a second round that is not full costs more than it gives
+// (24.6k tokens as 48 items of 64-key splits 26.3 us, as 24 of 128 23.2). A batch with a conversation of
+// one item keeps its plan: where all are, the split writes the outputs without a merge (600 tokens 9.7
+// us, cut 12.3). A conversation of at most 1024 tokens is one item in every plan of plan_decode, so its
+// bits do not depend on the batch it is decoded in; a longer one's do.
 DecodePlan plan_decode_filling(const std::vector<int32_t>& slots, const std::vector<int64_t>& lens,
                                int32_t n_kv_heads, int64_t target_items, int32_t n_cus);
 
@@ -132,8 +133,9 @@ struct ExtendConvDesc {
 
 constexpr int kExtendKeyTile = 64;  // keys per step of the attention kernel
 // Key tiles of the smallest piece; below, a piece is mostly start-up and records. One 64-token chunk on
-// 3000 tokens takes 22.1 us with 6, 24.1 with 8 (65 uncut), but a step of 8 conversations over 32 layers
-// 2134 / 2062 us and one of 4 over 28 layers in one launch 391 / 366, where other work fills the CUs.
+// 3000 tokens takes 19.6 us with 4, 22.0 with 8, but a step of 8 conversations over 32 layers 979 / 839 us,
+// one of 4 over 28 layers 407 / 337, and one of 8 over 16 layers in layer order 627 / 593, where other work
+// fills the CUs.
 constexpr int kMinPiece = 8;
 constexpr int kPieceStep = 4;       // a piece is a multiple of the buffers of the kernel's LDS ring
 
